@@ -1,0 +1,390 @@
+// Small-tile MFMA GEMMs: the products of gemm.hip (INT8 with the
+// dequantization epilogue or int32 output, bf16 with bias) for outputs that
+// have too few large tiles to fill 256 CUs, or too few rows to need them.
+//
+// What bounds these shapes is not the matrix cores but how many workgroups
+// pull the operands and how long the serial walk over K is: at 333 x 4096 x
+// 4096 the 192 x 128 tiles of gemm.hip give 64 workgroups, each with K / 128
+// steps in a row. Here a workgroup takes a tile of 16 x 16 to 128 x 128 and
+// splits it over its waves three ways: WM x WN wave tiles of 16 TJ x 16 TI,
+// times WK groups that take every WK-th K tile of 128 bytes. The WK partial
+// tiles meet in LDS at the end and are added in a fixed order, so no
+// workgroup waits for another and equal inputs give equal bits (int32 sums
+// are exact in any order). Measured against the kernels that ran these shapes
+// before (us in a graph of launches; int8 unless noted): 64 x 512 x 256 5.9
+// -> 2.8, 16 x 4096 x 4096 19.4 -> 5.1, 333 x 4096 x 4096 20.4 -> 13.3,
+// 128 x 4096 x 16384 72 -> 24, 100 x 100 x 16384 62 -> 7.4; bf16 4608 x 64 x
+// 4096 35 -> 11, 32 x 12288 x 4096 36 -> 17 (5.9 TB/s of weights).
+//
+//   global -> LDS: direct-to-LDS buffer loads of 16 bytes per lane, 8 rows x
+//     128 bytes per instruction, chunk c of row r at chunk c ^ ((r >> 1) & 7)
+//     (conflict-free 16-byte fragment reads). Whole 128-byte lines per row:
+//     fragments loaded straight into registers (16 rows x 64 bytes per
+//     instruction) moved about 25 bytes per clock and CU and lost above 16
+//     tokens.
+//   pipeline: a ring of STAGES stages of WK K tiles, one barrier per stage.
+//     Loads past K read as zeros (both operands), so K need only be a
+//     multiple of 64 bytes; rows past M and N read as zeros too.
+//   MFMA: v_mfma_i32_16x16x64_i8 / v_mfma_f32_16x16x32_bf16, W the first
+//     operand: an accumulator quad is 4 consecutive channels of one token.
+//   epilogue: through LDS, so that a group of lanes writes whole rows.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "internal.h"
+#include "row_io.h"
+
+namespace w8a8 {
+namespace {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+
+constexpr uint32_t kOutOfRange = 0x80000000u;  // past any num_records used here
+
+struct I8 {
+    using Acc = v4i;
+    __device__ static Acc mma(v4i a, v4i b, Acc c) {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+    }
+};
+struct Bf16 {
+    using Acc = v4f;
+    __device__ static Acc mma(v4i a, v4i b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a),
+                                                       __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+    }
+};
+
+enum Flags { kMFast = 1, kNVec = 2 };
+enum Epilogue { kDequantBf16 = 0, kStoreI32 = 1, kBiasBf16 = 2 };
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Workgroup -> tile. Workgroups go round-robin to the 8 XCDs, so each XCD gets
+// a contiguous range of tiles; m_fast walks the token tiles of one channel
+// panel first (the W panel is then read into one XCD's L2 only), else the
+// channel tiles of one token panel.
+__device__ __forceinline__ void map_tile(int pid, int tiles_m, int tiles_n, bool m_fast, int &tm,
+                                         int &tn) {
+    constexpr int kXcd = 8;
+    const int total = tiles_m * tiles_n;
+    const int full = total - total % kXcd;
+    const int lid = pid < full ? (pid % kXcd) * (full / kXcd) + pid / kXcd : pid;
+    if (m_fast) {
+        tn = lid / tiles_m;
+        tm = lid - tn * tiles_m;
+    } else {
+        tm = lid / tiles_n;
+        tn = lid - tm * tiles_n;
+    }
+}
+
+// Sums the WK partial tiles in LDS (in order) and writes the tile: quads of 4
+// channels, whole rows per group of lanes.
+template <class Op, int BM, int BN, int RS, int WK, int NT, int EPI>
+__device__ __forceinline__ void reduce_store(const float *red, const float *__restrict__ xs,
+                                             const float *__restrict__ ws,
+                                             const uint16_t *__restrict__ bias, int M, int N,
+                                             int m0, int n0, void *__restrict__ Yout, int flags) {
+    const bool n_vec = flags & kNVec;
+    for (int q = threadIdx.x; q < BM * BN / 4; q += NT) {
+        const int row = q / (BN / 4), c = (q % (BN / 4)) * 4;
+        typename Op::Acc s = *reinterpret_cast<const typename Op::Acc *>(red + row * RS + c);
+#pragma unroll
+        for (int w = 1; w < WK; ++w)
+            s += *reinterpret_cast<const typename Op::Acc *>(red + (w * BM + row) * RS + c);
+        const int m = m0 + row, n = n0 + c;
+        if (m >= M || n >= N) continue;
+        const int64_t at = static_cast<int64_t>(m) * N + n;
+        if constexpr (EPI == kStoreI32) {
+            int32_t *y = static_cast<int32_t *>(Yout) + at;
+            if (n_vec) {
+                *reinterpret_cast<v4i *>(y) = __builtin_bit_cast(v4i, s);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) y[e] = static_cast<int32_t>(s[e]);
+            }
+        } else {
+            float wsc[4] = {0.f, 0.f, 0.f, 0.f}, bb[4] = {0.f, 0.f, 0.f, 0.f};
+            if (n_vec) {
+                if constexpr (EPI == kDequantBf16) {
+                    const float4 w4 = *reinterpret_cast<const float4 *>(ws + n);
+                    wsc[0] = w4.x;
+                    wsc[1] = w4.y;
+                    wsc[2] = w4.z;
+                    wsc[3] = w4.w;
+                }
+                if (bias != nullptr) {
+                    const uint2 b2 = *reinterpret_cast<const uint2 *>(bias + n);
+                    bb[0] = __uint_as_float(b2.x << 16);
+                    bb[1] = __uint_as_float(b2.x & 0xffff0000u);
+                    bb[2] = __uint_as_float(b2.y << 16);
+                    bb[3] = __uint_as_float(b2.y & 0xffff0000u);
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (n + e >= N) continue;
+                    if constexpr (EPI == kDequantBf16) wsc[e] = ws[n + e];
+                    if (bias != nullptr)
+                        bb[e] = __uint_as_float(static_cast<uint32_t>(bias[n + e]) << 16);
+                }
+            }
+            float xv = 0.0f;
+            if constexpr (EPI == kDequantBf16) xv = xs[m];
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float a = static_cast<float>(s[e]);
+                if constexpr (EPI == kDequantBf16)
+                    y[e] = __builtin_fmaf(a, xv * wsc[e], bb[e]);
+                else
+                    y[e] = a + bb[e];
+            }
+            uint16_t *o = static_cast<uint16_t *>(Yout) + at;
+            const uint32_t p01 = bf16_pair(y[0], y[1]), p23 = bf16_pair(y[2], y[3]);
+            if (n_vec) {
+                *reinterpret_cast<v2u *>(o) = v2u{p01, p23};
+            } else {
+                const uint32_t h[4] = {p01, p01 >> 16, p23, p23 >> 16};
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (n + e < N) o[e] = static_cast<uint16_t>(h[e]);
+            }
+        }
+    }
+}
+
+// s_waitcnt with only vmcnt constrained.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+}
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+// Workgroup barrier without a memory fence (which would drain the prefetch);
+// the waits before it order the LDS accesses.
+__device__ __forceinline__ void barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+#define LDS_AS __attribute__((address_space(3)))
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, int8_t *lds, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LDS_AS void *)lds, 16, off, 0, 0, 0);
+}
+
+template <class Op, int TJ, int TI, int WM, int WN, int WK, int STAGES, int EPI>
+__global__ __launch_bounds__(WM *WN *WK * 64) void gemm_small_kernel(
+    const int8_t *__restrict__ X, const int8_t *__restrict__ W, const float *__restrict__ xs,
+    const float *__restrict__ ws, const uint16_t *__restrict__ bias, int M, int N, int Kb,
+    void *__restrict__ Yout, int tiles_m, int tiles_n, int flags) {
+    constexpr int NW = WM * WN * WK;
+    constexpr int BM = 16 * TJ * WM, BN = 16 * TI * WN;
+    constexpr int RS = BN + 4;
+    constexpr int GROUP = (BM + BN) * 128;   // one K tile: X rows, then W rows
+    constexpr int STAGE = GROUP * WK;
+    constexpr int BLK_G = GROUP / 1024;      // DMA blocks (8 rows) per K tile
+    constexpr int LOADS = STAGE / 1024 / NW;
+    static_assert(LOADS * NW * 1024 == STAGE && BLK_G % LOADS == 0, "DMA split");
+    constexpr int RED = WK * BM * RS * 4;
+    constexpr int LDS = STAGES * STAGE > RED ? STAGES * STAGE : RED;
+    static_assert(LDS <= 160 * 1024, "LDS");
+    __shared__ __attribute__((aligned(1024))) int8_t smem[LDS];
+
+    int tm, tn;
+    map_tile(blockIdx.x, tiles_m, tiles_n, flags & kMFast, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = rows::wave_index();
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
+    const int rows_x = min(BM, M - m0), rows_w = min(BN, N - n0);
+    const __amdgpu_buffer_rsrc_t rx = rows::make_rsrc(X + static_cast<int64_t>(m0) * Kb,
+                                                      static_cast<uint32_t>(rows_x) * Kb);
+    const __amdgpu_buffer_rsrc_t rw = rows::make_rsrc(W + static_cast<int64_t>(n0) * Kb,
+                                                      static_cast<uint32_t>(rows_w) * Kb);
+
+    // DMA: wave w loads blocks w LOADS.. of the stage, all of one K tile
+    const int g = wave * LOADS / BLK_G;          // the K tile of the stage
+    const int b0 = wave * LOADS - g * BLK_G;     // its first block there
+    uint32_t off[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int b = b0 + i, row = b * 8 + (lane >> 3);
+        off[i] = static_cast<uint32_t>(b < BM / 8 ? row : row - BM) * static_cast<uint32_t>(Kb) +
+                 (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    }
+    const auto issue = [&](int st) {
+        int8_t *slot = smem + (st % STAGES) * STAGE + g * GROUP;
+        const int kb = (st * WK + g) * 128;
+        if (kb + 128 <= Kb) {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i)
+                dma16(b0 + i < BM / 8 ? rx : rw, slot + (b0 + i) * 1024, off[i] + kb);
+        } else {
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) {
+                const int row = (b0 + i) * 8 + (lane >> 3);
+                const int kpos = kb + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+                dma16(b0 + i < BM / 8 ? rx : rw, slot + (b0 + i) * 1024,
+                      kpos < Kb ? off[i] + kb : kOutOfRange);
+            }
+        }
+    };
+
+    typename Op::Acc acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = typename Op::Acc{};
+
+    const int stages = (Kb + 128 * WK - 1) / (128 * WK);
+#pragma unroll
+    for (int s = 0; s < STAGES - 1; ++s) issue(s);
+    const int xrow = wm * 16 * TJ + r16, wrow = BM + wn * 16 * TI + r16;
+    const int key = (r16 >> 1) & 7;
+    // At the barrier of stage st every wave has its own loads of stage st in
+    // LDS and has finished reading stage st - 1, whose slot the loads of stage
+    // st + STAGES - 1 then fill (past the last stage they write zeros).
+    for (int st = 0; st < stages; ++st) {
+        wait_vmcnt<LOADS *(STAGES - 2)>();
+        barrier();
+        const int8_t *slot = smem + (st % STAGES) * STAGE + wk * GROUP;
+        v4i wf[2][TI], xf[2][TJ];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int chunk = ((4 * s + kg) ^ key) * 16;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+                wf[s][i] = *reinterpret_cast<const v4i *>(slot + (wrow + 16 * i) * 128 + chunk);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+                xf[s][j] = *reinterpret_cast<const v4i *>(slot + (xrow + 16 * j) * 128 + chunk);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        issue(st + STAGES - 1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+                    acc[i][j] = Op::mma(wf[s][i], xf[s][j], acc[i][j]);
+        wait_lgkmcnt0();
+    }
+    wait_vmcnt<0>();
+    barrier();
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+            *reinterpret_cast<v4i *>(red + (wk * BM + xrow + 16 * j) * RS + wn * 16 * TI + 16 * i +
+                                     4 * kg) = __builtin_bit_cast(v4i, acc[i][j]);
+    __syncthreads();
+    reduce_store<Op, BM, BN, RS, WK, NW * 64, EPI>(red, xs, ws, bias, M, N, m0, n0, Yout, flags);
+}
+
+// --------------------------------------------------------------------------
+// choice and launch
+// --------------------------------------------------------------------------
+
+// The tiles and, for each, the four constants of its time in us:
+//   a + e (n - 1) + KT max(l ceil(n / r), q n),
+// with n = tiles per CU (rounded up, at least 1), KT = K tiles of 128 bytes
+// and r = workgroups a CU holds (160 KB of LDS): start-up, epilogue per
+// further tile, the latency of a K tile in one workgroup and the time of one
+// when the CU is full. Fitted to the measured times of 190 shapes with
+// M 1..4608, N 64..24576 (N % 8 == 0), K 64..16384, log-uniform, both types
+// (each tile within 9-13% rms).
+struct SmallTile {
+    int bm, bn, threads, r;
+    double a, e, l, q;
+};
+constexpr SmallTile kSmall[] = {
+    {16, 16, 256, 2, 2.54, 0.69, 0.0328, 0.0449},
+    {32, 32, 256, 1, 2.79, 1.54, 0.0993, 0.0},
+    {32, 64, 512, 1, 3.03, 1.80, 0.1438, 0.0},
+    {64, 32, 256, 1, 3.31, 2.33, 0.1565, 0.0},
+    {64, 64, 512, 2, 2.63, 1.40, 0.3376, 0.1963},
+    {96, 64, 512, 2, 3.19, 1.78, 0.3743, 0.2422},
+    {128, 64, 512, 2, 3.55, 1.73, 0.0, 0.3061},
+    {128, 128, 512, 1, 4.89, 5.25, 0.0, 0.4767},
+};
+constexpr int kSmallTiles = sizeof(kSmall) / sizeof(kSmall[0]);
+
+template <class Op, int TJ, int TI, int WM, int WN, int WK, int STAGES, int EPI>
+hipError_t launch(const GemmArgs &a) {
+    constexpr int BM = 16 * TJ * WM, BN = 16 * TI * WN;
+    int tiles_m = (a.M + BM - 1) / BM;
+    int tiles_n = (a.N + BN - 1) / BN;
+    // 4 channels as one store: N % 4 == 0 and the vectors aligned. The tiles
+    // walk along the larger operand last, so that its panels are read once.
+    int flags = (a.N >= a.M ? kMFast : 0) |
+                (a.N % 4 == 0 && (reinterpret_cast<uintptr_t>(a.ws) & 15) == 0 &&
+                         (reinterpret_cast<uintptr_t>(a.bias) & 7) == 0
+                     ? kNVec
+                     : 0);
+    hipLaunchKernelGGL((gemm_small_kernel<Op, TJ, TI, WM, WN, WK, STAGES, EPI>),
+                       dim3(static_cast<unsigned>(tiles_m) * static_cast<unsigned>(tiles_n)),
+                       dim3(WM * WN * WK * 64), 0, a.stream, a.X, a.W, a.xs, a.ws, a.bias, a.M,
+                       a.N, a.Kb, a.Y, tiles_m, tiles_n, flags);
+    return hipGetLastError();
+}
+
+// One instance per entry of kSmall, in its order.
+template <class Op, int EPI>
+hipError_t launch_tile(int tile, const GemmArgs &a) {
+    switch (tile) {
+    case 0: return launch<Op, 1, 1, 1, 1, 4, 4, EPI>(a);
+    case 1: return launch<Op, 2, 2, 1, 1, 4, 3, EPI>(a);
+    case 2: return launch<Op, 1, 2, 2, 2, 2, 4, EPI>(a);
+    case 3: return launch<Op, 4, 2, 1, 1, 4, 3, EPI>(a);
+    case 4: return launch<Op, 2, 2, 2, 2, 2, 2, EPI>(a);
+    case 5: return launch<Op, 3, 2, 2, 2, 2, 2, EPI>(a);
+    case 6: return launch<Op, 2, 2, 4, 2, 1, 3, EPI>(a);
+    case 7: return launch<Op, 2, 4, 4, 2, 1, 3, EPI>(a);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+int pick_small_gemm(int64_t M, int64_t N, int64_t Kb, double *us) {
+    const double kt = static_cast<double>((Kb + 127) / 128);
+    int best = -1;
+    for (int c = 0; c < kSmallTiles; ++c) {
+        const SmallTile &t = kSmall[c];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (tiles * t.threads >= (INT64_C(1) << 32)) continue;  // not launchable
+        const int64_t n = (tiles + 255) / 256;
+        const int64_t turns = (n + t.r - 1) / t.r;
+        const double full = t.q * static_cast<double>(n), lat = t.l * static_cast<double>(turns);
+        const double est =
+            t.a + t.e * static_cast<double>(n - 1) + kt * (full > lat ? full : lat);
+        if (best < 0 || est < *us) {
+            best = c;
+            *us = est;
+        }
+    }
+    return best;
+}
+
+hipError_t launch_gemm_small(int tile, GemmKind kind, const GemmArgs &a) {
+    switch (kind) {
+    case GemmKind::kI8Bf16: return launch_tile<I8, kDequantBf16>(tile, a);
+    case GemmKind::kI8I32: return launch_tile<I8, kStoreI32>(tile, a);
+    default: return launch_tile<Bf16, kBiasBf16>(tile, a);
+    }
+}
+
+}  // namespace w8a8

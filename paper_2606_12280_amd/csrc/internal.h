@@ -83,8 +83,26 @@ hipError_t launch_gemm_bf16(const uint16_t *A, const uint16_t *B,
                             const uint16_t *bias, int64_t M, int64_t N,
                             int64_t K, uint16_t *Y, hipStream_t stream);
 
-// The tile (tokens x channels) and threads per workgroup of the GEMM the
-// two launchers above run for M x N with K bytes per row (host only).
+// The small-tile GEMMs that the two launchers above use where they are faster
+// than the large tiles (gemm_small.hip). pick_small_gemm gives the best small
+// tile for M x N with Kb bytes per row and its estimated time in us.
+struct GemmArgs {
+    const int8_t *X;
+    const int8_t *W;
+    const float *xs;
+    const float *ws;
+    const uint16_t *bias;
+    int M, N, Kb;
+    void *Y;
+    hipStream_t stream;
+};
+enum class GemmKind { kI8Bf16, kI8I32, kBf16 };
+int pick_small_gemm(int64_t M, int64_t N, int64_t Kb, double *us);
+hipError_t launch_gemm_small(int tile, GemmKind kind, const GemmArgs &a);
+
+// The large tile (tokens x channels) and threads per workgroup chosen for
+// M x N with K bytes per row, before the small tiles are considered (host
+// only).
 void gemm_config(int64_t M, int64_t N, int64_t Kb, int *tile_m, int *tile_n, int *threads);
 
 }  // namespace w8a8

@@ -269,6 +269,59 @@ def test_every_gemm_configuration(shape, config):
     check_bf16_output(Yb[rows], c["X"].reshape(M, K)[rows], c["W"].reshape(N, K), c["bias"])
 
 
+# Shapes that the small tiles take (gemm_small.hip): for each tile its edges
+# (one row or channel less, equal, one more), N odd and N % 4 == 0, K from one
+# 64-byte step to several ring turns with a half K tile left over, and outputs
+# of more tiles than CUs.
+SMALL_SHAPES = [(1, 1, 64), (16, 16, 128), (17, 15, 192), (100, 100, 4160),     # 16 x 16
+                (1, 8190, 64), (33, 1500, 1088), (31, 1000, 2048),              # 32 x 32
+                (1, 12000, 320), (33, 12001, 448), (3000, 63, 4096),            # 32 x 64
+                (4571, 65, 1024), (4545, 66, 2112),                             # 64 x 32
+                (65, 12000, 64), (4571, 127, 2112), (300, 4095, 832),           # 64 x 64, 128 x 64
+                (97, 12000, 64), (777, 2000, 192), (333, 4100, 1024),           # 128 x 64
+                (129, 16376, 320), (200, 15999, 576)]                        # 128 x 128
+
+
+@pytest.mark.parametrize("M,N,K", SMALL_SHAPES)
+def test_small_tile_gemms_whole_outputs(M, N, K):
+    """The small-tile kernels on whole outputs between guard bands: int32
+    accumulators bit-exact, the dequantizing epilogue within tolerance with and
+    without a bias and with w_scale and bias at
+    the smallest alignment the entry points accept, and bf16_linear within the
+    binary32 summation bound."""
+    A = synth.rand_i8([140, M, K], (M, K))
+    B = synth.rand_i8([141, N, K], (N, K))
+    acc = oracle.gemm_i32(A, B, M, N, K)
+    Ad, Bd = dev(A), dev(B)
+    pad = 1024
+    Cbuf = torch.full((M * N + 2 * pad,), 0x5A5A5A5A, dtype=torch.int32, device="cuda")
+    C = Cbuf[pad:pad + M * N].view(M, N)
+    ops.w8a8_gemm_i32(Ad, Bd, out=C)
+    assert np.array_equal(host(C), acc)
+    assert bool((Cbuf[:pad] == 0x5A5A5A5A).all()) and bool((Cbuf[pad + M * N:] == 0x5A5A5A5A).all())
+    rng = np.random.default_rng([142, M, N, K])
+    xs = rng.uniform(1e-3, 1e-1, M).astype(np.float32)
+    ws = rng.uniform(1e-4, 1e-2, N).astype(np.float32)
+    b = synth.rand_bf16([143, N], (N,), 0.5)
+    zero = np.zeros(N, np.uint16)
+    Ybuf = torch.full((M * N + 2 * pad,), 0x1234, dtype=torch.int16, device="cuda")
+    Y = Ybuf[pad:pad + M * N].view(torch.bfloat16).view(M, N)
+    wsd, bd = torch.zeros(N + 1, device="cuda"), torch.zeros(N + 1, device="cuda").bfloat16()
+    wsd[1:] = dev(ws)
+    bd[1:] = dev_bf16(b)
+    for bias, w, bits in ((dev_bf16(b), dev(ws), b), (None, dev(ws), zero), (bd[1:], wsd[1:], b)):
+        ops.w8a8_linear(Ad, dev(xs), Bd, w, bias, out=Y)
+        check_w8a8_output(host_bits(Y), oracle.epilogue(acc, xs, ws, bits, M, N), acc, xs, ws, bits)
+    c = synth.linear_case([144, M, N, K], M, N, K)
+    Xd, Wd = dev_bf16(c["X"].reshape(M, K)), dev_bf16(c["W"].reshape(N, K))
+    ops.bf16_linear(Xd, Wd, dev_bf16(c["bias"]), out=Y)
+    Yb = host_bits(Y)
+    rows = np.unique(np.concatenate([[0, M - 1], rng.choice(M, min(M, 130), replace=False)]))
+    check_bf16_output(Yb[rows], c["X"].reshape(M, K)[rows], c["W"].reshape(N, K), c["bias"])
+    g = host(Ybuf)
+    assert np.all(g[:pad] == 0x1234) and np.all(g[pad + M * N:] == 0x1234)
+
+
 @pytest.mark.parametrize("M,N,K", LARGE_RAGGED)
 def test_gemm_i32_large_ragged(M, N, K):
     A = synth.rand_i8([109, M, K], (M, K))
