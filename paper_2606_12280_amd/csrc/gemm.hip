@@ -90,6 +90,18 @@ __device__ __forceinline__ uint32_t f32x2_to_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
+// 8 channels n.. of output row m where rows start at any even address (N % 8
+// != 0): one 16-byte store (vector memory instructions take any element-
+// aligned address). As 2-byte stores, whose lanes lay 16 bytes apart, the
+// 192 x 256 kernel took 50 us at 4545 x 4350 x 384 (24 now).
+__device__ __forceinline__ void store_row16(void *Y, int m, int N, int n, v4i v) {
+    struct __attribute__((packed, aligned(2))) Row16 {
+        uint32_t w[4];
+    };
+    *reinterpret_cast<Row16 *>(static_cast<uint16_t *>(Y) + static_cast<int64_t>(m) * N + n) =
+        __builtin_bit_cast(Row16, v);
+}
+
 // s_waitcnt with only vmcnt constrained (gfx9 encoding: vmcnt[3:0] in bits
 // 3:0 and vmcnt[5:4] in bits 15:14; expcnt and lgkmcnt left at their maxima).
 template <int N>
@@ -444,6 +456,8 @@ struct Epi {
             const uint32_t base = static_cast<uint32_t>(mbase + row) * N;
             if (vec8 && n + 8 <= N) {
                 __builtin_amdgcn_raw_buffer_store_b128(v, ry, (base + n) * 2u, 0, 0);
+            } else if (n + 8 <= N) {
+                if (mbase + row < rows_x) store_row16(Yout, m0 + mbase + row, N, n, v);
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -452,66 +466,6 @@ struct Epi {
                         static_cast<uint16_t>(static_cast<uint32_t>(v[e >> 1]) >> (16 * (e & 1))),
                         ry, off, 0, 0);
                 }
-            }
-        }
-    }
-
-    // store_slices with the operands read from their LDS copy as each
-    // group of four channels is converted (tile-local token mbase.., channel
-    // nbase..; n0 is the tile's first channel), not held in registers for
-    // the whole epilogue. N % 8 == 0.
-    template <class Acc>
-    __device__ __forceinline__ void store_slices_lds(const Acc (&acc)[TI][TJ], int8_t *stage,
-                                                     const float *xs_l, const float *ws_l,
-                                                     const uint16_t *b_l, void *Yout, int m0,
-                                                     int rows_x, int mbase, int nbase, int n0,
-                                                     int N, int frow, int fhalf, int lane) const {
-        static_assert(EPI != kStoreI32, "row stores are for the bf16 epilogues");
-        constexpr int CPR = 64 * TI / 16;  // 16-byte chunks per row
-        constexpr int ROUNDS = 32 * CPR / 64;
-        static_assert(32 * CPR % 64 == 0, "whole store rounds");
-        const __amdgpu_buffer_rsrc_t ry =
-            make_rsrc(static_cast<int8_t *>(Yout) + static_cast<int64_t>(m0) * N * 2,
-                      static_cast<uint32_t>(rows_x) * N * 2u);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            const float xv = EPI == kDequantBf16 ? xs_l[mbase + 32 * j + frow] : 0.0f;
-#pragma unroll
-            for (int i = 0; i < TI; ++i)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int c = 32 * i + 8 * g + 4 * fhalf;
-                    float4 w4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    if constexpr (EPI == kDequantBf16)
-                        w4 = *reinterpret_cast<const float4 *>(ws_l + nbase + c);
-                    uint2 b2 = make_uint2(0u, 0u);
-                    if constexpr (HAS_BIAS) b2 = *reinterpret_cast<const uint2 *>(b_l + nbase + c);
-                    const float wv[4] = {w4.x, w4.y, w4.z, w4.w};
-                    const uint32_t bw[2] = {b2.x, b2.y};
-                    float y[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = static_cast<float>(acc[i][j][4 * g + e]);
-                        const float b =
-                            __uint_as_float((e & 1) ? (bw[e >> 1] & 0xffff0000u) : (bw[e >> 1] << 16));
-                        if constexpr (EPI == kDequantBf16)
-                            y[e] = __builtin_fmaf(a, xv * wv[e], b);
-                        else
-                            y[e] = a + b;
-                    }
-                    *reinterpret_cast<v2u *>(stage + frow * kRowStride + c * 2) =
-                        v2u{f32x2_to_bf16x2(y[0], y[1]), f32x2_to_bf16x2(y[2], y[3])};
-                }
-#pragma unroll
-            for (int r = 0; r < ROUNDS; ++r) {
-                const int id = r * 64 + lane;
-                const int row = id / CPR;
-                const int c = id % CPR;
-                const v4i v = *reinterpret_cast<const v4i *>(stage + row * kRowStride + c * 16);
-                const int n = n0 + nbase + 8 * c;
-                const uint32_t base = static_cast<uint32_t>(mbase + 32 * j + row) * N;
-                const uint32_t off = n + 8 <= N ? (base + n) * 2u : kOutOfRange;
-                __builtin_amdgcn_raw_buffer_store_b128(v, ry, off, 0, 0);
             }
         }
     }
@@ -567,6 +521,9 @@ struct Epi {
                 const uint32_t base = static_cast<uint32_t>(mbase + 32 * j + row) * N;
                 if (vec8 && n + 8 <= N) {
                     __builtin_amdgcn_raw_buffer_store_b128(v, ry, (base + n) * 2u, 0, 0);
+                } else if (n + 8 <= N) {
+                    if (mbase + 32 * j + row < rows_x)
+                        store_row16(Yout, m0 + mbase + 32 * j + row, N, n, v);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -788,7 +745,8 @@ struct Epi16 {
     // then stored as whole rows: 16 bytes per lane, 8 lanes per 128-byte row.
     // A wave's LDS accesses execute in order, so the row reads of slice j - 1
     // are done before slice j is written over them. The operand copies hold
-    // zeros past N; where N % 8 != 0 the rows go out element by element.
+    // zeros past N; where N % 8 != 0 the rows go out as unaligned stores, the
+    // last channels one by one.
     template <class Acc>
     __device__ __forceinline__ void store_slices_lds(const Acc (&acc)[TI][2][TJ][2],
                                                      int8_t *stage, const float *xs_l,
@@ -846,9 +804,12 @@ struct Epi16 {
                 const v4i v = *reinterpret_cast<const v4i *>(stage + row * kRowStride + c * 16);
                 const int n = n0 + nbase + 8 * c;
                 const uint32_t base = static_cast<uint32_t>(mbase + 32 * j + row) * N;
-                if (vec8 || n + 8 <= N) {
+                if (vec8) {
                     const uint32_t off = n + 8 <= N ? (base + n) * 2u : kOutOfRange;
                     __builtin_amdgcn_raw_buffer_store_b128(v, ry, off, 0, 0);
+                } else if (n + 8 <= N) {
+                    if (mbase + 32 * j + row < rows_x)
+                        store_row16(Yout, m0 + mbase + 32 * j + row, N, n, v);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
