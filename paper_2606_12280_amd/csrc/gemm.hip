@@ -35,7 +35,8 @@
 //   epilogue: y = float(acc) * (x_scale[m] * w_scale[n]) + bias[n] with one
 //     fma, four channels packed into 8 bytes of bf16 per store.
 //
-// Three kernels share this skeleton:
+// Two kernels share this skeleton (outputs too small for their tiles run on
+// those of gemm_small.hip):
 //   gemm_2s_kernel  large tiles (288 x 256 with 12 waves, 192 x 256 with 8)
 //                   in two-slot rings; four of the waves also issue the tile
 //                   loads. The default wherever its tiles fill the CUs, and
@@ -46,9 +47,7 @@
 //                   fragments and run MFMAs. With one wave doing both, the
 //                   in-order issue stalls the MFMA stream whenever the load
 //                   path pushes back; split across waves that share a SIMD,
-//                   loads and MFMAs proceed side by side. Small outputs;
-//   gemm_kernel     every wave loads and multiplies (used when the K tile is
-//                   64 bytes, i.e. K not a multiple of 128 bytes).
+//                   loads and MFMAs proceed side by side. Smaller outputs.
 //
 // Launch order is XCD-aware: workgroups are dispatched round-robin over the
 // 8 XCDs, so block id b runs on XCD b % 8. Each XCD is given a contiguous
@@ -234,71 +233,7 @@ struct Epi {
     float ws_[TI][4][4];
     uint32_t b_[TI][4][2];  // bf16 pairs, converted when stored
 
-    __device__ __forceinline__ void load(const float *xs, const float *ws, const uint16_t *bias,
-                                         int m0, int rows_x, int mbase, int nbase, int N, int frow,
-                                         int fhalf) {
-        // Range-checked loads (zero past M / N, or for a missing bias): no
-        // branch, and nothing consumes them before the epilogue.
-        const __amdgpu_buffer_rsrc_t rxs =
-            make_rsrc(EPI == kDequantBf16 ? xs + m0 : nullptr,
-                      EPI == kDequantBf16 ? static_cast<uint32_t>(rows_x) * 4u : 0u);
-        const __amdgpu_buffer_rsrc_t rws =
-            make_rsrc(ws, EPI == kDequantBf16 ? static_cast<uint32_t>(N) * 4u : 0u);
-        const __amdgpu_buffer_rsrc_t rbs =
-            make_rsrc(bias, HAS_BIAS ? static_cast<uint32_t>(N) * 2u : 0u);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            const uint32_t ml = mbase + 32 * j + frow;
-            xs_[j] = __builtin_bit_cast(float,
-                                        __builtin_amdgcn_raw_buffer_load_b32(rxs, ml * 4u, 0, 0));
-        }
-#pragma unroll
-        for (int i = 0; i < TI; ++i)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const uint32_t n = nbase + 32 * i + 8 * g + 4 * fhalf;
-                if constexpr (N_VEC) {
-                    // N % 4 == 0 (and w_scale / bias aligned): the 4 channels are all
-                    // inside or all outside; outside, a valid address is read and
-                    // discarded. (Plain vector loads: extracting the elements of a
-                    // 128-bit buffer load through bit casts miscompiles with this
-                    // compiler, which narrows the load to its first dword.)
-                    const bool ok = static_cast<int>(n) < N;
-                    const uint32_t nc = ok ? n : 0u;
-                    if constexpr (EPI == kDequantBf16) {
-                        const float4 w4 = *reinterpret_cast<const float4 *>(ws + nc);
-                        ws_[i][g][0] = ok ? w4.x : 0.0f;
-                        ws_[i][g][1] = ok ? w4.y : 0.0f;
-                        ws_[i][g][2] = ok ? w4.z : 0.0f;
-                        ws_[i][g][3] = ok ? w4.w : 0.0f;
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) ws_[i][g][e] = 0.0f;
-                    }
-                    b_[i][g][0] = 0u;
-                    b_[i][g][1] = 0u;
-                    if constexpr (HAS_BIAS) {
-                        const uint2 b2 = *reinterpret_cast<const uint2 *>(bias + nc);
-                        b_[i][g][0] = ok ? b2.x : 0u;
-                        b_[i][g][1] = ok ? b2.y : 0u;
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        ws_[i][g][e] = __builtin_bit_cast(
-                            float, __builtin_amdgcn_raw_buffer_load_b32(rws, (n + e) * 4u, 0, 0));
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        b_[i][g][h] =
-                            __builtin_amdgcn_raw_buffer_load_b16(rbs, (n + 2 * h) * 2u, 0, 0) |
-                            static_cast<uint32_t>(__builtin_amdgcn_raw_buffer_load_b16(
-                                rbs, (n + 2 * h + 1) * 2u, 0, 0))
-                                << 16;
-                }
-            }
-    }
-
-    // The same operands from the LDS copy written by fill_lds() (tile-local
+    // The operands from their LDS copy, written by fill_lds() (tile-local
     // indices: token mbase.., channel nbase..).
     __device__ __forceinline__ void load_lds(const float *xs_l, const float *ws_l,
                                              const uint16_t *b_l, int mbase, int nbase, int frow,
@@ -953,118 +888,6 @@ __device__ __forceinline__ uint32_t dma_offset(int blk, int lane, int Kb) {
 }
 
 // --------------------------------------------------------------------------
-// gemm_kernel: every wave loads and multiplies.
-// --------------------------------------------------------------------------
-template <class Op, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int SWZ,
-          int GROUP_M, int EPI, bool N_VEC, bool HAS_BIAS>
-__global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_kernel(
-    const int8_t *__restrict__ X, const int8_t *__restrict__ W, const float *__restrict__ xs,
-    const float *__restrict__ ws, const uint16_t *__restrict__ bias, int M, int N, int Kb,
-    void *__restrict__ Yout, int tiles_m, int tiles_n) {
-    constexpr int NW = WAVES_M * WAVES_N;
-    constexpr int WTM = BM / WAVES_M;  // tokens per wave
-    constexpr int WTN = BN / WAVES_N;  // channels per wave
-    constexpr int TJ = WTM / 32;
-    constexpr int TI = WTN / 32;
-    constexpr int LA = BM * BK / 1024 / NW;  // 1 KiB DMA blocks per wave, X tile
-    constexpr int LB = BN * BK / 1024 / NW;  // ... W tile
-    constexpr int LOADS = LA + LB;
-    constexpr int STAGE = (BM + BN) * BK;
-    static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
-    static_assert(LA * NW * 1024 == BM * BK && LB * NW * 1024 == BN * BK, "DMA split");
-    static_assert(BK == 64 || BK == 128, "K tile of 64 or 128 bytes");
-    static_assert(STAGES >= 2 && LOADS * (STAGES - 2) < 64, "vmcnt range");
-    static_assert(STAGES * STAGE <= 160 * 1024, "LDS");
-
-    __shared__ __attribute__((aligned(1024))) int8_t smem[STAGES * STAGE];
-
-    // Materialize the epilogue's pointer arguments now: a scalar load of a
-    // kernel argument left pending into the main loop would make every LDS
-    // wait there a full lgkmcnt(0) (scalar loads complete out of order).
-    keep_args(xs, ws, bias, Yout);
-
-    int tm, tn;
-    map_tile<GROUP_M>(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    const int m0 = tm * BM;
-    const int n0 = tn * BN;
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int mbase = (wave / WAVES_N) * WTM;
-    const int nbase = (wave % WAVES_N) * WTN;
-    const int rows_x = min(BM, M - m0);
-    const int rows_w = min(BN, N - n0);
-
-    // Epilogue operands first, and kept older than every tile load: the vmcnt
-    // waits below count only tile loads as younger. (They are global loads
-    // and the tile loads write LDS, so nothing else orders them.)
-    Epi<TI, TJ, EPI, N_VEC, HAS_BIAS> epi;
-    epi.load(xs, ws, bias, m0, rows_x, mbase, n0 + nbase, N, lane & 31, lane >> 5);
-    sched_fence();
-
-    const __amdgpu_buffer_rsrc_t rx =
-        make_rsrc(X + static_cast<int64_t>(m0) * Kb, static_cast<uint32_t>(rows_x) * Kb);
-    const __amdgpu_buffer_rsrc_t rw =
-        make_rsrc(W + static_cast<int64_t>(n0) * Kb, static_cast<uint32_t>(rows_w) * Kb);
-    uint32_t off_x[LA], off_w[LB];
-#pragma unroll
-    for (int i = 0; i < LA; ++i) off_x[i] = dma_offset<BK, SWZ>(wave + i * NW, lane, Kb);
-#pragma unroll
-    for (int i = 0; i < LB; ++i) off_w[i] = dma_offset<BK, SWZ>(wave + i * NW, lane, Kb);
-
-    const int KT = Kb / BK;  // the launcher guarantees BK divides Kb
-    auto issue = [&](int kt) {
-        int8_t *slot = smem + (kt % STAGES) * STAGE;
-        const int kb = kt * BK;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) dma16(rx, slot + (wave + i * NW) * 1024, off_x[i] + kb);
-#pragma unroll
-        for (int i = 0; i < LB; ++i)
-            dma16(rw, slot + BM * BK + (wave + i * NW) * 1024, off_w[i] + kb);
-    };
-
-    Mma<Op, BM, BK, TI, TJ, SWZ> mma;
-    mma.init(lane, mbase, nbase);
-
-    // Prologue: tiles 0..STAGES-2 in flight; once tile 0 has landed the last
-    // slot is issued too and the first fragments are read.
-#pragma unroll
-    for (int t = 0; t < STAGES - 1; ++t)
-        if (t < KT) issue(t);
-    if (STAGES - 1 <= KT)
-        wait_vmcnt<LOADS * (STAGES - 2)>();
-    else
-        wait_vmcnt<0>();
-    barrier();
-    if (STAGES - 1 < KT) issue(STAGES - 1);
-    mma.load(smem, 0, 0);
-
-    // Tile boundary kt -> kt+1: every read of tile kt has completed (the last
-    // ones were issued a whole MFMA step ago); once this wave's loads of tile
-    // kt+1 are in and all waves meet, slot kt is refilled with tile
-    // kt+STAGES and tile kt+1's first fragments are read. The three loops are
-    // branch-free so that the compiler's own waits stay exact.
-    int kt = 0;
-    for (; kt + STAGES < KT; ++kt)  // refill as we go
-        mma.template tile<false>(smem + (kt % STAGES) * STAGE, [&] {
-            wait_lgkmcnt0();
-            wait_vmcnt<LOADS * (STAGES - 2)>();
-            barrier();
-            issue(kt + STAGES);
-            mma.load(smem + ((kt + 1) % STAGES) * STAGE, 0, 0);
-        });
-    for (; kt + 1 < KT; ++kt)  // drain the ring
-        mma.template tile<false>(smem + (kt % STAGES) * STAGE, [&] {
-            wait_lgkmcnt0();
-            wait_vmcnt<0>();
-            barrier();
-            mma.load(smem + ((kt + 1) % STAGES) * STAGE, 0, 0);
-        });
-    mma.template tile<true>(smem + (kt % STAGES) * STAGE, [] {});
-
-    epi.store(mma.acc, Yout, m0, rows_x, mbase, n0 + nbase, N, lane & 31, lane >> 5);
-}
-
-// --------------------------------------------------------------------------
 // gemm_2s_kernel: four loading waves, two-slot rings. Made for large tiles
 // (192 x 256: 27% fewer bytes per MFMA than 256 x 128; 288 x 256 with 12
 // waves: 19% fewer than 192 x 256) whose accumulators leave no registers
@@ -1081,7 +904,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_kernel(
 // ring.
 // --------------------------------------------------------------------------
 template <class Op, int BM, int BN, int WAVES_M, int WAVES_N, int SWZ, int GROUP_M, int EPI,
-          bool N_VEC, bool HAS_BIAS>
+          bool N_VEC, bool HAS_BIAS, bool TAIL>
 __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_2s_kernel(
     const int8_t *__restrict__ X, const int8_t *__restrict__ W, const float *__restrict__ xs,
     const float *__restrict__ ws, const uint16_t *__restrict__ bias, int M, int N, int Kb,
@@ -1135,7 +958,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_2s_kernel(
     const int nbase = (wave % WAVES_N) * WTN;
     const int rows_x = min(BM, M - m0);
     const int rows_w = min(BN, N - n0);
-    const int KT = Kb / BK;  // the launcher guarantees BK divides Kb
+    const int KT = (Kb + BK - 1) / BK;
 
     const __amdgpu_buffer_rsrc_t rx =
         make_rsrc(X + static_cast<int64_t>(m0) * Kb, static_cast<uint32_t>(rows_x) * Kb);
@@ -1150,13 +973,21 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_2s_kernel(
     for (int i = 0; i < LW; ++i) off_w[i] = dma_offset<BK, SWZ>(iw + i * NI, lane, Kb);
     auto xslot = [&](int kt) { return xring + (kt & 1) * XSLOT; };
     auto wslot = [&](int kt) { return wring + (kt & 1) * WSLOT; };
+    // The lane's offset within a K tile: the same in all its blocks, which lie
+    // 32 rows apart. Past K (a last tile of 64 bytes, TAIL) it reads zeros.
+    const uint32_t kpos = dma_offset<BK, SWZ>(iw, lane, 0);
+    auto k_off = [&](int kt) {
+        const uint32_t k = kt * BK;
+        if constexpr (TAIL) return kpos + k < static_cast<uint32_t>(Kb) ? k : kOutOfRange;
+        return k;
+    };
     // Load i of this wave's share of tile kt: W blocks first, then X blocks.
     auto issue_one = [&](int kt, int i) {
         if (!loader) return;
         if (i < LW)
-            dma16(rw, wslot(kt) + (iw + i * NI) * 1024, off_w[i] + kt * BK);
+            dma16(rw, wslot(kt) + (iw + i * NI) * 1024, off_w[i] + k_off(kt));
         else
-            dma16(rx, xslot(kt) + (iw + (i - LW) * NI) * 1024, off_x[i - LW] + kt * BK);
+            dma16(rx, xslot(kt) + (iw + (i - LW) * NI) * 1024, off_x[i - LW] + k_off(kt));
     };
 
     // Fragments two MFMA steps ahead at two waves per SIMD (32 x 32 blocks);
@@ -1209,13 +1040,17 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_2s_kernel(
     if constexpr (!AHEAD2) {
         Epi16<TI, TJ, EPI, N_VEC, HAS_BIAS> epi;
         static_assert(SLICED, "12 waves stage 32-token slices");
+        // lane-dependent addresses from an opaque copy of the lane id, so that
+        // none is computed before the K loop and held (or spilled) across it
+        int le = lane;
+        asm volatile("" : "+v"(le));
         if constexpr (EPI == kStoreI32) {
-            epi.store(mma.acc, Yout, m0, rows_x, mbase, n0 + nbase, N, lane);
+            epi.store(mma.acc, Yout, m0, rows_x, mbase, n0 + nbase, N, le);
         } else {
             wait_lgkmcnt0();
             barrier();  // every wave is done with the ring
             epi.store_slices_lds(mma.acc, smem + wave * STAGE_BYTES, ep_xs, ep_ws, ep_b, Yout,
-                                 m0, rows_x, mbase, nbase, n0, N, lane);
+                                 m0, rows_x, mbase, nbase, n0, N, le);
         }
     } else {
         EpiT epi;
@@ -1255,7 +1090,7 @@ __global__ __launch_bounds__(WAVES_M *WAVES_N * 64) void gemm_2s_kernel(
 // output slices (55 KB). Needs 256 <= K bytes, N % 8 == 0 and w_scale / bias
 // 16 / 8-byte aligned (the launcher checks).
 // --------------------------------------------------------------------------
-template <class Op, int EPI, bool HAS_BIAS>
+template <class Op, int EPI, bool HAS_BIAS, bool TAIL>
 __global__ __launch_bounds__(768) void gemm_pt_kernel(
     const int8_t *__restrict__ X, const int8_t *__restrict__ W, const float *__restrict__ xs,
     const float *__restrict__ ws, const uint16_t *__restrict__ bias, int M, int N, int Kb,
@@ -1293,10 +1128,11 @@ __global__ __launch_bounds__(768) void gemm_pt_kernel(
     const int nbase = (wave % WAVES_N) * WTN;
     const bool loader = wave < NI;
     const int iw = loader ? wave : 0;
-    const int KT = Kb / BK;  // >= 2, the launcher guarantees BK divides Kb
+    const int KT = (Kb + BK - 1) / BK;  // >= 2
     // Lane part of every DMA offset: block iw + i NI starts 32 i rows below
     // block iw, and the swizzle key of a row does not change over 32 rows.
     const uint32_t off0 = dma_offset<BK, SWZ>(iw, lane, Kb);
+    const uint32_t kpos = dma_offset<BK, SWZ>(iw, lane, 0);  // within a K tile, as in every block
     const uint32_t panel_step = static_cast<uint32_t>(NI * ROWS_PER_DMA) * Kb;
 
     auto slot_ptr = [&](int q) { return smem + (q & 1) * SLOT; };
@@ -1325,12 +1161,16 @@ __global__ __launch_bounds__(768) void gemm_pt_kernel(
         int8_t *slot = slot_ptr(q);
         uint32_t base = off0;
         asm volatile("" : "+v"(base));
+        uint32_t k = kt * BK;
+        if constexpr (TAIL) {  // past K (a last tile of 64 bytes): zeros
+            if (kpos + k >= static_cast<uint32_t>(Kb)) k = kOutOfRange;
+        }
         uint32_t step = panel_step;
         asm volatile("" : "+s"(step));
         if (i < LW)
-            dma16(tl.rw, slot + XSLOT + (iw + i * NI) * 1024, base + (i * step + kt * BK));
+            dma16(tl.rw, slot + XSLOT + (iw + i * NI) * 1024, base + (i * step + k));
         else
-            dma16(tl.rx, slot + (iw + (i - LW) * NI) * 1024, base + ((i - LW) * step + kt * BK));
+            dma16(tl.rx, slot + (iw + (i - LW) * NI) * 1024, base + ((i - LW) * step + k));
     };
     // The epilogue operands of `tl` into LDS (wave EPW; zero past M / N).
     auto issue_ep = [&](const Tile &tl) {
@@ -1437,10 +1277,9 @@ __global__ __launch_bounds__(768) void gemm_pt_kernel(
 //   between barrier #kt and #kt+1: consumers multiply tile kt; producers
 //     refill slot kt-1 (free: every consumer read of it completed before
 //     barrier #kt) with tile kt+STAGES-1, then wait for tile kt+1.
-// The launcher guarantees BK divides K (no K tail).
 // --------------------------------------------------------------------------
 template <class Op, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int NPROD, int STAGES,
-          int SWZ, int GROUP_M, int EPI, bool N_VEC, bool HAS_BIAS>
+          int SWZ, int GROUP_M, int EPI, bool N_VEC, bool HAS_BIAS, bool TAIL>
 __global__ __launch_bounds__((WAVES_M * WAVES_N + NPROD) * 64) void gemm_ws_kernel(
     const int8_t *__restrict__ X, const int8_t *__restrict__ W, const float *__restrict__ xs,
     const float *__restrict__ ws, const uint16_t *__restrict__ bias, int M, int N, int Kb,
@@ -1456,7 +1295,7 @@ __global__ __launch_bounds__((WAVES_M * WAVES_N + NPROD) * 64) void gemm_ws_kern
     constexpr int STAGE = (BM + BN) * BK;
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be whole 32x32 blocks");
     static_assert(LP * NPROD == NBX + NBW, "DMA split");
-    static_assert(BK == 64 || BK == 128, "K tile of 64 or 128 bytes");
+    static_assert(BK == 128 && SWZ == 1 && LP % 2 == 0, "a block's parity is its index's");
     static_assert(STAGES >= 2 && LP * (STAGES - 2) < 64, "vmcnt range");
     static_assert(STAGES * STAGE + 4 * BM + 6 * BN <= 160 * 1024, "LDS");
 
@@ -1478,7 +1317,7 @@ __global__ __launch_bounds__((WAVES_M * WAVES_N + NPROD) * 64) void gemm_ws_kern
     const int wave = wave_id();
     const int rows_x = min(BM, M - m0);
     const int rows_w = min(BN, N - n0);
-    const int KT = Kb / BK;
+    const int KT = (Kb + BK - 1) / BK;
 
     if (wave >= NC) {
         // ---------------- producer ----------------
@@ -1495,11 +1334,21 @@ __global__ __launch_bounds__((WAVES_M * WAVES_N + NPROD) * 64) void gemm_ws_kern
         }
         auto issue = [&](int t) {
             int8_t *slot = smem + (t % STAGES) * STAGE;
-            const int kb = t * BK;
+            // the K offset for blocks of either parity (whose lanes hold
+            // different chunks); past K (a last tile of 64 bytes) zeros
+            uint32_t kb[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                kb[h] = t * BK;
+                if constexpr (TAIL) {
+                    if (dma_offset<BK, SWZ>(h, lane, 0) + kb[h] >= static_cast<uint32_t>(Kb))
+                        kb[h] = kOutOfRange;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < LP; ++i) {
                 const int b = p * LP + i;  // X blocks first, then W blocks
-                dma16(b < NBX ? rx : rw, slot + b * 1024, off[i] + kb);
+                dma16(b < NBX ? rx : rw, slot + b * 1024, off[i] + kb[i & 1]);
             }
         };
 #pragma unroll
@@ -1567,7 +1416,9 @@ __global__ __launch_bounds__((WAVES_M * WAVES_N + NPROD) * 64) void gemm_ws_kern
 
 // The four instances of one configuration: vector epilogue operands (N % 4
 // == 0 with aligned w_scale / bias) or not, with or without a bias.
-template <template <bool, bool> class K>
+// (K<..., TAIL> for a K that is no multiple of 128 bytes: int8 only, a bf16 row
+// has twice 64 bytes.)
+template <template <bool, bool, bool> class K, bool MAY_TAIL>
 hipError_t dispatch(const GemmArgs &a, int EPI_is_i32, int BM, int BN, int threads) {
     int tiles_m = (a.M + BM - 1) / BM;
     int tiles_n = (a.N + BN - 1) / BN;
@@ -1575,8 +1426,15 @@ hipError_t dispatch(const GemmArgs &a, int EPI_is_i32, int BM, int BN, int threa
     const bool has_bias = !EPI_is_i32 && a.bias != nullptr;
     const bool n_vec = a.N % 4 == 0 && (reinterpret_cast<uintptr_t>(a.ws) & 15) == 0 &&
                        (reinterpret_cast<uintptr_t>(a.bias) & 7) == 0;
-    const void *fn = n_vec ? (has_bias ? K<true, true>::fn() : K<true, false>::fn())
-                           : (has_bias ? K<false, true>::fn() : K<false, false>::fn());
+    const void *fn = nullptr;
+    if (a.Kb % 128 == 0) {
+        fn = n_vec ? (has_bias ? K<true, true, false>::fn() : K<true, false, false>::fn())
+                   : (has_bias ? K<false, true, false>::fn() : K<false, false, false>::fn());
+    } else if constexpr (MAY_TAIL) {
+        fn = n_vec ? (has_bias ? K<true, true, true>::fn() : K<true, false, true>::fn())
+                   : (has_bias ? K<false, true, true>::fn() : K<false, false, true>::fn());
+    }
+    if (fn == nullptr) return hipErrorInvalidValue;
     const int8_t *X = a.X;
     const int8_t *W = a.W;
     const float *xs = a.xs;
@@ -1588,36 +1446,19 @@ hipError_t dispatch(const GemmArgs &a, int EPI_is_i32, int BM, int BN, int threa
     return hipLaunchKernel(fn, grid, dim3(threads), args, 0, a.stream);
 }
 
-template <class Op, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int STAGES, int SWZ,
-          int GROUP_M, int EPI>
-struct Uniform {
-    template <bool NV, bool HB>
-    struct K {
-        static const void *fn() {
-            return reinterpret_cast<const void *>(
-                &gemm_kernel<Op, BM, BN, BK, WAVES_M, WAVES_N, STAGES, SWZ, GROUP_M, EPI, NV, HB>);
-        }
-    };
-    static hipError_t launch(const GemmArgs &a) {
-        if (a.Kb % BK != 0) return hipErrorInvalidValue;
-        return dispatch<K>(a, EPI == kStoreI32, BM, BN, WAVES_M * WAVES_N * 64);
-    }
-};
-
 template <class Op, int BM, int BN, int BK, int WAVES_M, int WAVES_N, int NPROD, int STAGES,
           int SWZ, int GROUP_M, int EPI>
 struct Specialized {
-    template <bool NV, bool HB>
+    template <bool NV, bool HB, bool TAIL>
     struct K {
         static const void *fn() {
             return reinterpret_cast<const void *>(
                 &gemm_ws_kernel<Op, BM, BN, BK, WAVES_M, WAVES_N, NPROD, STAGES, SWZ, GROUP_M, EPI,
-                                NV, HB>);
+                                NV, HB, TAIL>);
         }
     };
     static hipError_t launch(const GemmArgs &a) {
-        if (a.Kb % BK != 0) return hipErrorInvalidValue;
-        return dispatch<K>(a, EPI == kStoreI32, BM, BN, (WAVES_M * WAVES_N + NPROD) * 64);
+        return dispatch<K, std::is_same_v<Op, I8Op>>(a, EPI == kStoreI32, BM, BN, (WAVES_M * WAVES_N + NPROD) * 64);
     }
 };
 
@@ -1641,15 +1482,19 @@ int persistent_grid() {
 template <class Op, int EPI>
 struct Persistent {
     template <bool HB>
-    static const void *fn() {
-        return reinterpret_cast<const void *>(&gemm_pt_kernel<Op, EPI, HB>);
+    static const void *fn(bool tail) {
+        if constexpr (std::is_same_v<Op, I8Op>) {
+            if (tail) return reinterpret_cast<const void *>(&gemm_pt_kernel<Op, EPI, HB, true>);
+        }
+        return tail ? nullptr
+                    : reinterpret_cast<const void *>(&gemm_pt_kernel<Op, EPI, HB, false>);
     }
     // Whether the persistent kernel takes this launch: whole rounds of
     // 288 x 256 tiles to walk, at least two K tiles, and the vector
     // epilogue's layout (N % 8 == 0, w_scale / bias aligned).
     static bool applies(const GemmArgs &a, int grid) {
         const int64_t tiles = static_cast<int64_t>((a.M + 287) / 288) * ((a.N + 255) / 256);
-        return grid >= 8 && tiles > grid && a.Kb % 128 == 0 && a.Kb >= 256 && a.N % 8 == 0 &&
+        return grid >= 8 && tiles > grid && a.Kb >= 256 && a.N % 8 == 0 &&
                (reinterpret_cast<uintptr_t>(a.ws) & 15) == 0 &&
                (reinterpret_cast<uintptr_t>(a.bias) & 7) == 0;
     }
@@ -1657,7 +1502,9 @@ struct Persistent {
         int tiles_m = (a.M + 287) / 288;
         int tiles_n = (a.N + 255) / 256;
         const bool has_bias = EPI != kStoreI32 && a.bias != nullptr;
-        const void *f = has_bias ? fn<true>() : fn<false>();
+        const bool tail = a.Kb % 128 != 0;
+        const void *f = has_bias ? fn<true>(tail) : fn<false>(tail);
+        if (f == nullptr) return hipErrorInvalidValue;
         const int8_t *X = a.X;
         const int8_t *W = a.W;
         const float *xs = a.xs;
@@ -1673,53 +1520,54 @@ struct Persistent {
 
 template <class Op, int BM, int BN, int WAVES_M, int WAVES_N, int SWZ, int GROUP_M, int EPI>
 struct TwoSlot {
-    template <bool NV, bool HB>
+    template <bool NV, bool HB, bool TAIL>
     struct K {
         static const void *fn() {
             return reinterpret_cast<const void *>(
-                &gemm_2s_kernel<Op, BM, BN, WAVES_M, WAVES_N, SWZ, GROUP_M, EPI, NV, HB>);
+                &gemm_2s_kernel<Op, BM, BN, WAVES_M, WAVES_N, SWZ, GROUP_M, EPI, NV, HB, TAIL>);
         }
     };
     static hipError_t launch(const GemmArgs &a) {
-        if (a.Kb % 128 != 0) return hipErrorInvalidValue;
-        return dispatch<K>(a, EPI == kStoreI32, BM, BN, WAVES_M * WAVES_N * 64);
+        return dispatch<K, std::is_same_v<Op, I8Op>>(a, EPI == kStoreI32, BM, BN, WAVES_M * WAVES_N * 64);
     }
 };
 
 // Default configurations.
-//  - K a multiple of 128 bytes (every DiT shape): the candidate that
-//    minimizes the estimated time, rounds of the 256 CUs (one workgroup per
-//    CU) x tile area / rate, where rate is the throughput per output
-//    element at full rounds, measured at 4608 x 4096 -> 16384 (where every
-//    candidate fills whole rounds) relative to the 288 x 256 tiles, whose
-//    16 x 16 MFMAs make them the fastest per element. Ties go to the earlier
-//    candidate.
-//    * 288 x 256 tiles (tokens x channels), two-slot, 12 waves of 96 x 64:
-//      at M = 4608 = 16 x 288 every DiT shape fills whole rounds (N = 16384:
-//      4, N = 12288: 3, N = 4096: 1);
-//    * 192 x 256, two-slot, 8 waves of 96 x 64;
-//    * 192 x 128 and 256 x 128, warp-specialized (4 consumer waves of 96 x
-//      64 or 128 x 64, 4 producer waves, 3-slot ring): the small tiles for
-//      outputs of fewer than a round of large tiles.
-//    All use 128-byte K tiles (full cache lines per row) and the swizzle key
-//    (row >> 1) & 7.
-//  - otherwise: every wave loads, 192 x 256 tiles, 4 waves of 192 x 64,
-//    4-slot ring of 64-byte K tiles (BK = 64 divides K), key (row >> 2) & 3.
+// The candidate that minimizes the estimated time, rounds of the 256 CUs (one
+// workgroup per CU) x tile area / rate, where rate is the throughput per
+// output element at full rounds, measured at 4608 x 4096 -> 16384 (where every
+// candidate fills whole rounds) relative to the 288 x 256 tiles, whose
+// 16 x 16 MFMAs make them the fastest per element. Ties go to the earlier
+// candidate.
+//  * 288 x 256 tiles (tokens x channels), two-slot, 12 waves of 96 x 64:
+//    at M = 4608 = 16 x 288 every DiT shape fills whole rounds (N = 16384:
+//    4, N = 12288: 3, N = 4096: 1);
+//  * 192 x 256, two-slot, 8 waves of 96 x 64;
+//  * 192 x 128 and 256 x 128, warp-specialized (4 consumer waves of 96 x
+//    64 or 128 x 64, 4 producer waves, 3-slot ring): for outputs of fewer than
+//    a round of large tiles.
+// All use 128-byte K tiles (full cache lines per row) and the swizzle key
+// (row >> 1) & 7. A K that ends in a tile of 64 bytes (int8, K % 128 == 64)
+// reads that tile's second half as zeros: a kernel of 64-byte K tiles (192 x
+// 256, 4 waves) took 45.8 us at 1117 x 8640 x 2880, these tiles 37.7, and 103
+// and 63.6 us at 4608 x 4096 x 4160.
+// Rows of K % 128 == 64 bytes start in the middle of a 128-byte line every
+// other time, which costs the smaller tiles more (half_rate).
 struct TileChoice {
     int bm, bn, threads;
-    double rate;
+    double rate, half_rate;
 };
 constexpr TileChoice kTiles[] = {
-    {288, 256, 768, 1.0},
-    {192, 256, 512, 0.82},
-    {192, 128, 512, 0.71},
-    {256, 128, 512, 0.73},
+    {288, 256, 768, 1.0, 1.0},
+    {192, 256, 512, 0.82, 0.75},
+    {192, 128, 512, 0.71, 0.45},
+    {256, 128, 512, 0.73, 0.55},
 };
 constexpr int kTileChoices = sizeof(kTiles) / sizeof(kTiles[0]);
 
 // A candidate whose grid would reach 2^32 work-items is skipped; the first
 // never does within the entry points' limit M N <= 2^38.
-int pick_tiles(int M, int N) {
+int pick_tiles(int M, int N, int64_t Kb) {
     int best = 0;
     double best_t = 0.0;
     for (int c = 0; c < kTileChoices; ++c) {
@@ -1727,7 +1575,8 @@ int pick_tiles(int M, int N) {
         const int64_t tiles = static_cast<int64_t>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
         if (c > 0 && tiles * t.threads >= (INT64_C(1) << 32)) continue;
         const int64_t rounds = (tiles + 255) / 256;
-        const double est = static_cast<double>(rounds) * t.bm * t.bn / t.rate;
+        const double est = static_cast<double>(rounds) * t.bm * t.bn /
+                           (Kb % 128 == 0 ? t.rate : t.half_rate);
         if (c == 0 || est < best_t) {
             best = c;
             best_t = est;
@@ -1738,21 +1587,22 @@ int pick_tiles(int M, int N) {
 
 // Estimated time in us of the large tile that the rule above picks: start-up
 // plus, per round of the CUs, an epilogue and Kb / 128 K tiles (fitted to the
-// measured times of 190 shapes, see gemm_small.hip; the 64-byte kernel's two
-// K tiles of 64 bytes count as one).
+// measured times of 190 shapes, see gemm_small.hip).
 double large_us(int M, int N, int Kb) {
     struct Fit {
         double a, e, c;
     };
     constexpr Fit kFit[kTileChoices] = {{10.2, 4.3, 1.53}, {6.64, 7.07, 1.14},
                                         {5.48, 1.51, 0.485}, {7.14, 1.75, 0.804}};
-    const bool uniform = Kb % 128 != 0;
-    const int c = uniform ? 1 : pick_tiles(M, N);
-    const Fit f = uniform ? Fit{8.74, 10.4, 1.12} : kFit[c];
+    // per K tile where K % 128 == 64
+    constexpr double kHalf[kTileChoices] = {1.65, 1.35, 0.85, 1.1};
+    const int c = pick_tiles(M, N, Kb);
+    const Fit f = kFit[c];
     const int64_t tiles = static_cast<int64_t>((M + kTiles[c].bm - 1) / kTiles[c].bm) *
                           ((N + kTiles[c].bn - 1) / kTiles[c].bn);
     const double rounds = static_cast<double>((tiles + 255) / 256);
-    return f.a + f.e * (rounds - 1.0) + rounds * f.c * static_cast<double>((Kb + 127) / 128);
+    return f.a + f.e * (rounds - 1.0) + rounds * (Kb % 128 == 0 ? f.c : kHalf[c]) *
+                                           static_cast<double>((Kb + 127) / 128);
 }
 
 template <class Op, int EPI>
@@ -1771,22 +1621,19 @@ hipError_t launch_default(const GemmArgs &a) {
                                                              : GemmKind::kBf16;
         return launch_gemm_small(small, kind, a);
     }
-    if (a.Kb % 128 == 0) {
-        switch (pick_tiles(a.M, a.N)) {
-        case 0: {
-            const int grid = persistent_grid();
-            if (Persistent<Op, EPI>::applies(a, grid)) return Persistent<Op, EPI>::launch(a, grid);
-            return TwoSlot<Op, 288, 256, 3, 4, 1, 8, EPI>::launch(a);
-        }
-        case 1:
-            return TwoSlot<Op, 192, 256, 2, 4, 1, 4, EPI>::launch(a);
-        case 2:
-            return Specialized<Op, 192, 128, 128, 2, 2, 4, 3, 1, 4, EPI>::launch(a);
-        default:
-            return Specialized<Op, 256, 128, 128, 2, 2, 4, 3, 1, 4, EPI>::launch(a);
-        }
+    switch (pick_tiles(a.M, a.N, a.Kb)) {
+    case 0: {
+        const int grid = persistent_grid();
+        if (Persistent<Op, EPI>::applies(a, grid)) return Persistent<Op, EPI>::launch(a, grid);
+        return TwoSlot<Op, 288, 256, 3, 4, 1, 8, EPI>::launch(a);
     }
-    return Uniform<Op, 192, 256, 64, 1, 4, 4, 2, 4, EPI>::launch(a);
+    case 1:
+        return TwoSlot<Op, 192, 256, 2, 4, 1, 4, EPI>::launch(a);
+    case 2:
+        return Specialized<Op, 192, 128, 128, 2, 2, 4, 3, 1, 4, EPI>::launch(a);
+    default:
+        return Specialized<Op, 256, 128, 128, 2, 2, 4, 3, 1, 4, EPI>::launch(a);
+    }
 }
 
 }  // namespace
@@ -1821,12 +1668,13 @@ hipError_t launch_gemm_bf16(const uint16_t *A, const uint16_t *B, const uint16_t
 }
 
 void gemm_config(int64_t M, int64_t N, int64_t Kb, int *tile_m, int *tile_n, int *threads) {
-    if (Kb % 128 == 0) {
-        const TileChoice &t = kTiles[pick_tiles(static_cast<int>(M), static_cast<int>(N))];
-        *tile_m = t.bm;
-        *tile_n = t.bn;
-        *threads = t.threads;
-    } else {
+    const TileChoice &t = kTiles[pick_tiles(static_cast<int>(M), static_cast<int>(N), Kb)];
+    *tile_m = t.bm;
+    *tile_n = t.bn;
+    *threads = t.threads;
+    // Far too few large tiles and K % 128 == 64 (always run on small tiles):
+    // the answer stays the one this call has always given there.
+    if (Kb % 128 != 0 && ((M + 191) / 192) * ((N + 127) / 128) < 64) {
         *tile_m = 192;
         *tile_n = 256;
         *threads = 256;

@@ -233,6 +233,12 @@ def test_gemm_i32_bit_exact(M, N, K):
 LARGE_RAGGED = [(4571, 16376, 128), (4600, 16375, 256), (4545, 12290, 384),
                 (4608, 16384, 640)]
 
+# K % 128 == 64 (a last K tile of 64 bytes) on each large tile: persistent
+# 288 x 256, 288 x 256 with N odd and with a single K tile, 192 x 256,
+# 192 x 128 and 256 x 128.
+HALF_TILE_SHAPES = [(4571, 16376, 320), (4600, 16375, 192), (4571, 16376, 64),
+                    (4545, 4350, 448), (2000, 2000, 1088), (1000, 8190, 320)]
+
 # One ragged shape per GEMM configuration, with the (tile_m, tile_n,
 # threads) the library reports for it.
 CONFIG_SHAPES = [
@@ -322,7 +328,7 @@ def test_small_tile_gemms_whole_outputs(M, N, K):
     assert np.all(g[:pad] == 0x1234) and np.all(g[pad + M * N:] == 0x1234)
 
 
-@pytest.mark.parametrize("M,N,K", LARGE_RAGGED)
+@pytest.mark.parametrize("M,N,K", LARGE_RAGGED + HALF_TILE_SHAPES)
 def test_gemm_i32_large_ragged(M, N, K):
     A = synth.rand_i8([109, M, K], (M, K))
     B = synth.rand_i8([110, N, K], (N, K))
@@ -331,7 +337,7 @@ def test_gemm_i32_large_ragged(M, N, K):
     assert np.array_equal(C, ref)
 
 
-@pytest.mark.parametrize("M,N,K", LARGE_RAGGED)
+@pytest.mark.parametrize("M,N,K", LARGE_RAGGED + HALF_TILE_SHAPES)
 @pytest.mark.parametrize("with_bias", [True, False])
 def test_w8a8_linear_large_ragged(M, N, K, with_bias):
     """The dequantizing epilogue (rows staged through LDS) on whole outputs."""
