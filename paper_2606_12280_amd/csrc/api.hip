@@ -311,9 +311,8 @@ w8a8_status q8_0_linear(const uint16_t *X, const int8_t *qs, const uint16_t *d,
                          {{X, 2 * M * K}, {qs, N * K}, {d, N * (K / 32) * 2},
                           {bias, bias ? 2 * N : 0}}));
     if (M == 0) return W8A8_OK;
-    const hipStream_t s = as_stream(stream);
-    W8A8_TRY(hip_status(w8a8::launch_q8_0_dequantize(qs, d, N, K, work, s)));
-    return hip_status(w8a8::launch_gemm_bf16(X, work, bias, M, N, K, Y, s));
+    return hip_status(
+        w8a8::launch_q8_0_linear(X, qs, d, bias, M, N, K, work, Y, as_stream(stream)));
 }
 
 // Q4_K plane sizes in bytes for W [N][K].
@@ -375,9 +374,8 @@ w8a8_status q4_k_linear(const uint16_t *X, const uint8_t *qs, const uint8_t *sca
                          {{X, 2 * M * K}, {qs, b.qs}, {scales, b.scales}, {d, b.super},
                           {dmin, b.super}, {bias, bias ? 2 * N : 0}}));
     if (M == 0) return W8A8_OK;
-    const hipStream_t s = as_stream(stream);
-    W8A8_TRY(hip_status(w8a8::launch_q4_k_dequantize(qs, scales, d, dmin, N, K, work, s)));
-    return hip_status(w8a8::launch_gemm_bf16(X, work, bias, M, N, K, Y, s));
+    return hip_status(w8a8::launch_q4_k_linear(X, qs, scales, d, dmin, bias, M, N, K, work, Y,
+                                               as_stream(stream)));
 }
 
 }  // extern "C"

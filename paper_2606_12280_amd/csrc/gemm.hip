@@ -1605,20 +1605,29 @@ double large_us(int M, int N, int Kb) {
                                            static_cast<double>((Kb + 127) / 128);
 }
 
+// The small tile that runs M x N with Kb bytes per row, or -1 for the large
+// tiles; *us is the estimate of the one chosen. Small tiles where their
+// estimate is at least 15% below the large tile's: both are within about 10%
+// of the measured time. Over the 190 shapes they were fitted to, no shape got
+// slower by this rule, the time fell to 0.58 of the large tiles' (geometric
+// mean), and the choice is 1.4% off the fastest of all tiles. (At 0.95, two
+// shapes got slower, one by 7%.)
+int choose_small(int64_t M, int64_t N, int64_t Kb, double *us) {
+    const double large = large_us(static_cast<int>(M), static_cast<int>(N), static_cast<int>(Kb));
+    const int small = pick_small_gemm(M, N, Kb, us);
+    if (small >= 0 && *us < 0.85 * large) return small;
+    *us = large;
+    return -1;
+}
+
 template <class Op, int EPI>
 hipError_t launch_default(const GemmArgs &a) {
-    // The small tiles where their estimate is at least 15% below the large
-    // tile's: both estimates are within about 10% of the measured time. Over
-    // the 190 shapes they were fitted to, no shape got slower by this rule,
-    // the time fell to 0.58 of the large tiles' (geometric mean), and the
-    // choice is 1.4% off the fastest of all tiles. (At 0.95, two shapes got
-    // slower, one by 7%.)
-    double small_us = 0.0;
-    const int small = pick_small_gemm(a.M, a.N, a.Kb, &small_us);
-    if (small >= 0 && small_us < 0.85 * large_us(a.M, a.N, a.Kb)) {
+    double us = 0.0;
+    const int small = choose_small(a.M, a.N, a.Kb, &us);
+    if (small >= 0) {
         constexpr GemmKind kind = EPI == kStoreI32      ? GemmKind::kI8I32
-                                       : EPI == kDequantBf16 ? GemmKind::kI8Bf16
-                                                             : GemmKind::kBf16;
+                                  : EPI == kDequantBf16 ? GemmKind::kI8Bf16
+                                                        : GemmKind::kBf16;
         return launch_gemm_small(small, kind, a);
     }
     switch (pick_tiles(a.M, a.N, a.Kb)) {
@@ -1665,6 +1674,12 @@ hipError_t launch_gemm_bf16(const uint16_t *A, const uint16_t *B, const uint16_t
                Y,
                stream};
     return launch_default<Bf16Op, kBiasBf16>(a);
+}
+
+double gemm_estimate_us(int64_t M, int64_t N, int64_t Kb) {
+    double us = 0.0;
+    choose_small(M, N, Kb, &us);
+    return us;
 }
 
 void gemm_config(int64_t M, int64_t N, int64_t Kb, int *tile_m, int *tile_n, int *threads) {

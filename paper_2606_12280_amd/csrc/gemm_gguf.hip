@@ -1,0 +1,432 @@
+// GGUF linears: Y = X W'^T + bias with W' = decode(codes, scales), the bf16
+// weights that q8_0.hip and q4_k.hip define. For few tokens the weights are
+// decoded inside the GEMM instead of into memory first.
+//
+// Decoding into memory writes 2 bytes and reads 2 again per weight for every
+// 1.06 (Q8_0) or 0.56 (Q4_K) read; with few tokens those bytes are the time.
+// Here a workgroup takes BM tokens x BN channels and streams the codes of its
+// channels once; each token tile decodes them again, so this pays up to a few
+// hundred tokens (see pick_tile). Times of decode + GEMM before and of this
+// kernel, us: Q8_0 1 x 12288 x 4096 54 -> 16.3, 30 x 4096 x 4096 34 -> 9.5,
+// 154 x 12288 x 4096 73 -> 36; Q4_K 20 x 20000 x 1024 35 -> 14.6, 100 x 4096 x
+// 4096 35 -> 18. With one token the chain of a stage (codes from LDS, decode,
+// weights to LDS, barrier, fragments) bounds it, which is why narrow tiles,
+// whose stages hold more of K, win there; with more the matrix cores wait for
+// the decoding waves.
+//
+//   global -> LDS: X rows (swizzled as in gemm_small.hip) and the raw codes
+//     (linear) by direct-to-LDS loads in a ring of S stages; the scales by
+//     ordinary loads one stage ahead.
+//   decode: the 512 threads decode stage st + 1 with the very operations of
+//     the decode kernels, 8 bytes of codes each, and write bf16 into one of two
+//     W slots while the MFMAs of stage st run. A stage holds as much of K as
+//     that gives each of the BN channels: 64 weights (Q8_0) or 128 (Q4_K) at
+//     64 channels, four times as many at 16.
+//   MFMA: as in gemm_small.hip; WM x WN wave tiles times WK wave groups that
+//     share a stage's K, added in LDS in a fixed order at the end.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "internal.h"
+#include "small_tile.h"
+
+namespace w8a8 {
+namespace {
+
+using namespace small;
+
+typedef unsigned int v2u __attribute__((ext_vector_type(2)));
+
+constexpr int kThreads = 512;
+
+__device__ __forceinline__ float half_bits(uint32_t h) {
+    return static_cast<float>(__builtin_bit_cast(_Float16, static_cast<uint16_t>(h)));
+}
+
+struct Planes {
+    const uint8_t *qs;
+    const uint8_t *scales;  // Q4_K
+    const uint16_t *d;
+    const uint16_t *dmin;   // Q4_K
+};
+
+// The W chunk (16 bytes, 8 weights) c of channel `row` in a W slot of BN
+// channels: sub-tiles of 64 weights, swizzled like X.
+template <int BN>
+__device__ __forceinline__ v4i *w_chunk(int8_t *w, int row, int c) {
+    return reinterpret_cast<v4i *>(w + (c >> 3) * (BN * 128) + row * 128 +
+                                   (((c & 7) ^ ((row >> 1) & 7)) << 4));
+}
+
+// A decoder: how a thread turns 8 bytes of codes, its share of a channel in a
+// stage, into weights. E weights at offset k of the row.
+struct Q8 {
+    static constexpr int E = 8;  // weights per thread and stage
+    struct Scale {
+        uint32_t d;
+    };
+    __amdgpu_buffer_rsrc_t rd;
+    uint32_t off;
+    __device__ __forceinline__ void init(const Planes &p, int n0, int rows_w, int K, int row) {
+        rd = rows::make_rsrc(p.d + static_cast<int64_t>(n0) * (K / 32),
+                             static_cast<uint32_t>(rows_w) * (K / 32) * 2u);
+        off = static_cast<uint32_t>(row) * (K / 32) * 2u;
+    }
+    __device__ __forceinline__ Scale load(int k) const {
+        return Scale{__builtin_amdgcn_raw_buffer_load_b16(rd, off + (k >> 5) * 2u, 0, 0)};
+    }
+    template <int BN>
+    __device__ __forceinline__ static void decode(v2u q, int8_t *w, int row, int part, int,
+                                                  const Scale &s) {
+        const float ds = half_bits(s.d);
+        uint32_t out[4];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int32_t v = static_cast<int32_t>(q[i]);
+            out[2 * i] = bf16_pair(ds * static_cast<float>((v << 24) >> 24),
+                                   ds * static_cast<float>((v << 16) >> 24));
+            out[2 * i + 1] = bf16_pair(ds * static_cast<float>((v << 8) >> 24),
+                                       ds * static_cast<float>(v >> 24));
+        }
+        *w_chunk<BN>(w, row, part) =
+            v4i{static_cast<int>(out[0]), static_cast<int>(out[1]), static_cast<int>(out[2]),
+                static_cast<int>(out[3])};
+    }
+};
+
+struct Q4 {
+    static constexpr int E = 16;
+    struct Scale {
+        uint32_t w0, w1, w2, d, dm;
+    };
+    __amdgpu_buffer_rsrc_t rs, rd, rm;
+    uint32_t soff, doff;
+    __device__ __forceinline__ void init(const Planes &p, int n0, int rows_w, int K, int row) {
+        const int64_t first = static_cast<int64_t>(n0) * (K / 256);
+        const uint32_t n = static_cast<uint32_t>(rows_w) * (K / 256);
+        rs = rows::make_rsrc(p.scales + first * 12, n * 12u);
+        rd = rows::make_rsrc(p.d + first, n * 2u);
+        rm = rows::make_rsrc(p.dmin + first, n * 2u);
+        soff = static_cast<uint32_t>(row) * (K / 256) * 12u;
+        doff = static_cast<uint32_t>(row) * (K / 256) * 2u;
+    }
+    __device__ __forceinline__ Scale load(int k) const {
+        const uint32_t g = k >> 8;
+        Scale s;
+        s.w0 = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + g * 12u, 0, 0);
+        s.w1 = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + g * 12u + 4u, 0, 0);
+        s.w2 = __builtin_amdgcn_raw_buffer_load_b32(rs, soff + g * 12u + 8u, 0, 0);
+        s.d = __builtin_amdgcn_raw_buffer_load_b16(rd, doff + g * 2u, 0, 0);
+        s.dm = __builtin_amdgcn_raw_buffer_load_b16(rm, doff + g * 2u, 0, 0);
+        return s;
+    }
+    template <int BN>
+    __device__ __forceinline__ static void decode(v2u q, int8_t *w, int row, int part, int k,
+                                                  const Scale &c) {
+        const int j = (k >> 5) & 7;  // sub-block
+        const int sh = 8 * (j & 3);
+        const uint32_t lo = (c.w2 >> sh) & 255u;
+        const uint32_t vs =
+            j < 4 ? (c.w0 >> sh) & 63u : (lo & 15u) | (((c.w0 >> (sh + 6)) & 3u) << 4);
+        const uint32_t vm =
+            j < 4 ? (c.w1 >> sh) & 63u : (lo >> 4) | (((c.w1 >> (sh + 6)) & 3u) << 4);
+        const float s = half_bits(c.d) * static_cast<float>(vs);
+        const float o = half_bits(c.dm) * static_cast<float>(vm);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            int out[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float q0 = static_cast<float>((q[i] >> (8 * e)) & 15u);
+                const float q1 = static_cast<float>((q[i] >> (8 * e + 4)) & 15u);
+                out[e] = static_cast<int>(bf16_pair(s * q0 - o, s * q1 - o));
+            }
+            *w_chunk<BN>(w, row, 2 * part + i) = v4i{out[0], out[1], out[2], out[3]};
+        }
+    }
+};
+
+template <class Dec, int TJ, int TI, int WM, int WN, int S>
+__global__ __launch_bounds__(kThreads) void gemm_gguf_kernel(
+    const int8_t *__restrict__ X, Planes p, const uint16_t *__restrict__ bias, int M, int N, int K,
+    void *__restrict__ Yout, int tiles_m, int tiles_n) {
+    constexpr int BM = 16 * TJ * WM, BN = 16 * TI * WN;
+    constexpr int PARTS = kThreads / BN;     // threads that decode a channel
+    constexpr int KE = PARTS * Dec::E;       // weights of a channel per stage
+    constexpr int RAW = PARTS * 8;           // ... and bytes of codes
+    constexpr int WK = 8 / (WM * WN);        // wave groups along K
+    constexpr int STEPS = KE / 32 / WK;      // MFMA steps per wave and stage
+    constexpr int SUB = KE / 64;             // 128-byte sub-tiles of X and W
+    constexpr int RS = BN + 4;
+    static_assert(WK * WM * WN == 8 && STEPS >= 1, "8 waves");
+    constexpr int XBLK = BM * SUB / 8;       // 1 KiB DMA blocks of X per stage
+    constexpr int QBLK = 4;                  // ... of codes: 8 bytes per thread
+    constexpr int LOADS = (XBLK + QBLK + 7) / 8;
+    constexpr int STAGE = (XBLK + QBLK) * 1024;
+    constexpr int WSLOT = BN * KE * 2;
+    constexpr int RING = S * STAGE, PAD = RING + 2 * WSLOT;
+    // A wave whose share of blocks is short sends an empty load to the pad, so
+    // that every wave has the same number in flight.
+    constexpr bool HAS_PAD = (XBLK + QBLK) % 8 != 0;
+    constexpr int RED = WK * BM * RS * 4;
+    constexpr int USED = PAD + (HAS_PAD ? 1024 : 0);
+    constexpr int LDS = USED > RED ? USED : RED;
+    static_assert(LDS <= 160 * 1024 && S >= 3, "LDS");
+    __shared__ __attribute__((aligned(1024))) int8_t smem[LDS];
+
+    int tm, tn;
+    map_tile(blockIdx.x, tiles_m, tiles_n, true, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = rows::wave_index();
+    const int r16 = lane & 15, kg = lane >> 4;
+    const int wk = wave / (WM * WN), wm = wave / WN % WM, wn = wave % WN;
+    const int rows_x = min(BM, M - m0), rows_w = min(BN, N - n0);
+    const uint32_t xrow_bytes = 2u * static_cast<uint32_t>(K);
+    const uint32_t qrow_bytes = static_cast<uint32_t>(K) / Dec::E * 8u;
+    const __amdgpu_buffer_rsrc_t rx = rows::make_rsrc(
+        X + static_cast<int64_t>(m0) * xrow_bytes, static_cast<uint32_t>(rows_x) * xrow_bytes);
+    const __amdgpu_buffer_rsrc_t rq = rows::make_rsrc(
+        p.qs + static_cast<int64_t>(n0) * qrow_bytes, static_cast<uint32_t>(rows_w) * qrow_bytes);
+    const int KT = (K + KE - 1) / KE;
+
+    // The wave's blocks: wave, wave + 8, ... of the X blocks (8 rows x 128
+    // bytes of one sub-tile), then the code blocks (linear). at[i] is the
+    // lane's byte in its row at stage 0, off[i] its offset in the panel.
+    uint32_t off[LOADS], at[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int b = wave + 8 * i;
+        if (b < XBLK) {
+            const int row = b % (BM / 8) * 8 + (lane >> 3);
+            at[i] = (b / (BM / 8)) * 128u + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+            off[i] = static_cast<uint32_t>(row) * xrow_bytes + at[i];
+        } else {
+            const int byte = (b - XBLK) * 1024 + lane * 16;
+            at[i] = byte % RAW;
+            off[i] = static_cast<uint32_t>(byte / RAW) * qrow_bytes + at[i];
+        }
+    }
+    const auto issue = [&](int st) {
+        int8_t *slot = smem + st % S * STAGE;
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int b = wave + 8 * i;
+            const bool isx = b < XBLK;
+            const bool real = !HAS_PAD || b < XBLK + QBLK;
+            const uint32_t step = static_cast<uint32_t>(st) * (isx ? KE * 2u : RAW);
+            // past the row's end: zeros
+            const bool in = real && at[i] + step < (isx ? xrow_bytes : qrow_bytes);
+            dma16(isx ? rx : rq, real ? slot + b * 1024 : smem + PAD,
+                  in ? off[i] + step : kOutOfRange);
+        }
+    };
+
+    // decoding: thread t has channel t / PARTS, part t % PARTS
+    const int drow = threadIdx.x / PARTS, part = threadIdx.x % PARTS;
+    Dec dec;
+    dec.init(p, n0, rows_w, K, drow);
+    // (past the row's end the last weights' scales, for codes and X of zero)
+    const auto scales = [&](int st) { return dec.load(min(st * KE + part * Dec::E, K - 1)); };
+    const auto decode = [&](int st, const typename Dec::Scale &sc) {
+        const v2u q = *reinterpret_cast<const v2u *>(smem + st % S * STAGE + XBLK * 1024 +
+                                                     threadIdx.x * 8);
+        Dec::template decode<BN>(q, smem + RING + (st & 1) * WSLOT, drow, part,
+                                 st * KE + part * Dec::E, sc);
+    };
+
+    v4f acc[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] = v4f{};
+
+    typename Dec::Scale sc = scales(0);
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) issue(s);
+    wait_vmcnt<LOADS *(S - 2)>();
+    barrier();
+    decode(0, sc);
+    sc = scales(1);
+
+    const int xrow = wm * 16 * TJ + r16, wrow = wn * 16 * TI + r16;
+    const int key = (r16 >> 1) & 7;
+    // Barrier of stage st: X of stage st, the codes of stage st + 1 and the
+    // decoded W of stage st are in LDS, and every wave has read stage st - 1:
+    // its ring slot takes stage st + S - 1, its W slot stage st + 1. The scales
+    // of stage st + 2 are loaded before the ring's loads, so that waiting for
+    // them leaves those in flight.
+    for (int st = 0; st < KT; ++st) {
+        wait_vmcnt<LOADS *(S - 3)>();
+        wait_lgkmcnt0();
+        barrier();
+        const int8_t *xs = smem + st % S * STAGE;
+        const int8_t *wslot = smem + RING + (st & 1) * WSLOT;
+        v4i wf[STEPS][TI], xf[STEPS][TJ];
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s) {
+            const int step = wk * STEPS + s;  // 32 weights each
+            const int chunk = (((step & 1) * 4 + kg) ^ key) * 16;
+            const int8_t *xt = xs + (step >> 1) * BM * 128 + chunk;
+            const int8_t *wt = wslot + (step >> 1) * BN * 128 + chunk;
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+                wf[s][i] = *reinterpret_cast<const v4i *>(wt + (wrow + 16 * i) * 128);
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+                xf[s][j] = *reinterpret_cast<const v4i *>(xt + (xrow + 16 * j) * 128);
+        }
+        const typename Dec::Scale sn = scales(st + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        issue(st + S - 1);
+#pragma unroll
+        for (int s = 0; s < STEPS; ++s)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int i = 0; i < TI; ++i)
+                    acc[i][j] = Bf16::mma(wf[s][i], xf[s][j], acc[i][j]);
+        if (st + 1 < KT) decode(st + 1, sc);
+        sc = sn;
+    }
+    wait_vmcnt<0>();
+    wait_lgkmcnt0();
+    barrier();
+    float *red = reinterpret_cast<float *>(smem);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j)
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+            *reinterpret_cast<v4f *>(red + (wk * BM + xrow + 16 * j) * RS + wn * 16 * TI + 16 * i +
+                                     4 * kg) = acc[i][j];
+    __syncthreads();
+    reduce_store<Bf16, BM, BN, RS, WK, kThreads, kBiasBf16>(red, nullptr, nullptr, bias, M, N, m0,
+                                                            n0, Yout);
+}
+
+template <class Dec, int TJ, int TI, int WM, int WN, int S>
+hipError_t launch(const uint16_t *X, const Planes &p, const uint16_t *bias, int64_t M, int64_t N,
+                  int64_t K, uint16_t *Y, hipStream_t stream) {
+    constexpr int BM = 16 * TJ * WM, BN = 16 * TI * WN;
+    const int tiles_m = static_cast<int>((M + BM - 1) / BM);
+    const int tiles_n = static_cast<int>((N + BN - 1) / BN);
+    hipLaunchKernelGGL((gemm_gguf_kernel<Dec, TJ, TI, WM, WN, S>),
+                       dim3(static_cast<unsigned>(tiles_m) * static_cast<unsigned>(tiles_n)),
+                       dim3(kThreads), 0, stream, reinterpret_cast<const int8_t *>(X), p, bias,
+                       static_cast<int>(M), static_cast<int>(N), static_cast<int>(K), Y, tiles_m,
+                       tiles_n);
+    return hipGetLastError();
+}
+
+// The tiles and, for each format, the constants of its time in us, a + e (n -
+// 1) + K / 64 max(l ceil(n / r), q n) as in gemm_small.hip, fitted to 80
+// shapes (M 1..1500, N 64..24576, K 256..16384, log-uniform): 4-8% rms. The
+// last Q4_K tile is 128 x 64, whose 128-byte sub-tiles fill the LDS.
+struct GgufTile {
+    int bm, bn, r;
+    double a, e, l, q;
+};
+constexpr int kGgufTiles = 8;
+constexpr GgufTile kGguf[2][kGgufTiles] = {
+    {{16, 16, 2, 2.76, 0.80, 0.0827, 0.0688},
+     {32, 16, 1, 3.04, 1.79, 0.0, 0.0991},
+     {16, 32, 3, 2.67, 0.28, 0.1463, 0.0955},
+     {32, 32, 2, 2.85, 0.87, 0.1680, 0.1411},
+     {64, 32, 1, 3.16, 2.18, 0.0, 0.1971},
+     {32, 64, 3, 2.56, 0.0, 0.2819, 0.2331},
+     {96, 64, 2, 3.34, 0.55, 0.3513, 0.3487},
+     {160, 64, 1, 3.66, 3.33, 0.0, 0.4683}},
+    {{16, 16, 1, 3.14, 1.90, 0.0, 0.0865},
+     {32, 16, 1, 3.49, 2.30, 0.0, 0.1008},
+     {16, 32, 1, 2.74, 1.55, 0.0, 0.1558},
+     {32, 32, 1, 2.80, 1.78, 0.0, 0.1799},
+     {64, 32, 1, 3.22, 2.32, 0.2182, 0.0895},
+     {32, 64, 1, 2.70, 1.82, 0.0, 0.3173},
+     {96, 64, 1, 3.52, 2.83, 0.0, 0.4015},
+     {128, 64, 1, 3.86, 3.26, 0.0, 0.4484}},
+};
+
+hipError_t launch_q8(int tile, const uint16_t *X, const Planes &p, const uint16_t *bias, int64_t M,
+                     int64_t N, int64_t K, uint16_t *Y, hipStream_t s) {
+    switch (tile) {
+    case 0: return launch<Q8, 1, 1, 1, 1, 4>(X, p, bias, M, N, K, Y, s);
+    case 1: return launch<Q8, 2, 1, 1, 1, 4>(X, p, bias, M, N, K, Y, s);
+    case 2: return launch<Q8, 1, 1, 1, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 3: return launch<Q8, 2, 1, 1, 2, 5>(X, p, bias, M, N, K, Y, s);
+    case 4: return launch<Q8, 4, 1, 1, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 5: return launch<Q8, 2, 1, 1, 4, 4>(X, p, bias, M, N, K, Y, s);
+    case 6: return launch<Q8, 3, 2, 2, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 7: return launch<Q8, 5, 2, 2, 2, 4>(X, p, bias, M, N, K, Y, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_q4(int tile, const uint16_t *X, const Planes &p, const uint16_t *bias, int64_t M,
+                     int64_t N, int64_t K, uint16_t *Y, hipStream_t s) {
+    switch (tile) {
+    case 0: return launch<Q4, 1, 1, 1, 1, 4>(X, p, bias, M, N, K, Y, s);
+    case 1: return launch<Q4, 2, 1, 1, 1, 3>(X, p, bias, M, N, K, Y, s);
+    case 2: return launch<Q4, 1, 1, 1, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 3: return launch<Q4, 2, 1, 1, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 4: return launch<Q4, 4, 1, 1, 2, 3>(X, p, bias, M, N, K, Y, s);
+    case 5: return launch<Q4, 2, 1, 1, 4, 4>(X, p, bias, M, N, K, Y, s);
+    case 6: return launch<Q4, 3, 2, 2, 2, 4>(X, p, bias, M, N, K, Y, s);
+    case 7: return launch<Q4, 4, 2, 2, 2, 3>(X, p, bias, M, N, K, Y, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// The tile to run at M x N x K, or -1 where decoding into memory and the plain
+// GEMM is faster: that pass moves 2 bytes per weight out and its codes in at
+// 2.8 TB/s after a start of 2.3 us (fitted). Decoding in the GEMM is taken
+// where its estimate is at least a tenth below; over 110 shapes the time then
+// fell to 0.65 of decode + GEMM (geometric mean). It stops paying at a few
+// hundred tokens of a wide layer (12288 x 4096: 73 -> 36 us at 154 tokens,
+// 109 -> 106 at 600 for Q8_0), where every token tile decodes again.
+int pick_tile(bool q4, int64_t M, int64_t N, int64_t K) {
+    int best = -1;
+    double best_us = 0.0;
+    for (int c = 0; c < kGgufTiles; ++c) {
+        const GgufTile &t = kGguf[q4 ? 1 : 0][c];
+        const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+        if (tiles * kThreads >= (INT64_C(1) << 32)) continue;  // not launchable
+        const int64_t n = (tiles + 255) / 256;
+        const int64_t turns = (n + t.r - 1) / t.r;
+        const double full = t.q * static_cast<double>(n), lat = t.l * static_cast<double>(turns);
+        const double us = t.a + t.e * static_cast<double>(n - 1) +
+                          static_cast<double>(K) / 64.0 * (full > lat ? full : lat);
+        if (best < 0 || us < best_us) {
+            best = c;
+            best_us = us;
+        }
+    }
+    const double bytes = static_cast<double>(N) * static_cast<double>(K) * (q4 ? 2.5625 : 3.0625);
+    const double decode_us = 2.3 + bytes / 2.8e6;
+    return best >= 0 && best_us < 0.9 * (decode_us + gemm_estimate_us(M, N, 2 * K)) ? best : -1;
+}
+
+}  // namespace
+
+hipError_t launch_q8_0_linear(const uint16_t *X, const int8_t *qs, const uint16_t *d,
+                              const uint16_t *bias, int64_t M, int64_t N, int64_t K,
+                              uint16_t *work, uint16_t *Y, hipStream_t stream) {
+    const int tile = pick_tile(false, M, N, K);
+    if (tile >= 0) {
+        const Planes p{reinterpret_cast<const uint8_t *>(qs), nullptr, d, nullptr};
+        return launch_q8(tile, X, p, bias, M, N, K, Y, stream);
+    }
+    const hipError_t e = launch_q8_0_dequantize(qs, d, N, K, work, stream);
+    return e != hipSuccess ? e : launch_gemm_bf16(X, work, bias, M, N, K, Y, stream);
+}
+
+hipError_t launch_q4_k_linear(const uint16_t *X, const uint8_t *qs, const uint8_t *scales,
+                              const uint16_t *d, const uint16_t *dmin, const uint16_t *bias,
+                              int64_t M, int64_t N, int64_t K, uint16_t *work, uint16_t *Y,
+                              hipStream_t stream) {
+    const int tile = pick_tile(true, M, N, K);
+    if (tile >= 0) return launch_q4(tile, X, Planes{qs, scales, d, dmin}, bias, M, N, K, Y, stream);
+    const hipError_t e = launch_q4_k_dequantize(qs, scales, d, dmin, N, K, work, stream);
+    return e != hipSuccess ? e : launch_gemm_bf16(X, work, bias, M, N, K, Y, stream);
+}
+
+}  // namespace w8a8

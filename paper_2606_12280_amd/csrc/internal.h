@@ -100,6 +100,20 @@ enum class GemmKind { kI8Bf16, kI8I32, kBf16 };
 int pick_small_gemm(int64_t M, int64_t N, int64_t Kb, double *us);
 hipError_t launch_gemm_small(int tile, GemmKind kind, const GemmArgs &a);
 
+// Estimated time in us of the GEMM that the two launchers run for M x N with
+// Kb bytes per row.
+double gemm_estimate_us(int64_t M, int64_t N, int64_t Kb);
+
+// The GGUF linears: weights decoded inside the GEMM for few tokens, else into
+// work [N][K] and from there (gemm_gguf.hip).
+hipError_t launch_q8_0_linear(const uint16_t *X, const int8_t *qs, const uint16_t *d,
+                              const uint16_t *bias, int64_t M, int64_t N, int64_t K,
+                              uint16_t *work, uint16_t *Y, hipStream_t stream);
+hipError_t launch_q4_k_linear(const uint16_t *X, const uint8_t *qs, const uint8_t *scales,
+                              const uint16_t *d, const uint16_t *dmin, const uint16_t *bias,
+                              int64_t M, int64_t N, int64_t K, uint16_t *work, uint16_t *Y,
+                              hipStream_t stream);
+
 // The large tile (tokens x channels) and threads per workgroup chosen for
 // M x N with K bytes per row, before the small tiles are considered (host
 // only).

@@ -1,0 +1,167 @@
+// Device helpers shared by the small-tile GEMMs (gemm_small.hip, gemm_gguf.hip):
+// MFMA operations, direct-to-LDS loads, explicit waits, the tile order and the
+// epilogue that adds a workgroup's partial tiles and writes whole rows.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "row_io.h"
+
+namespace w8a8 {
+namespace small {
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+
+constexpr uint32_t kOutOfRange = 0x80000000u;  // past any num_records used here
+
+struct I8 {
+    using Acc = v4i;
+    __device__ static Acc mma(v4i a, v4i b, Acc c) {
+        return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
+    }
+};
+struct Bf16 {
+    using Acc = v4f;
+    __device__ static Acc mma(v4i a, v4i b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a),
+                                                       __builtin_bit_cast(v8bf, b), c, 0, 0, 0);
+    }
+};
+
+enum Epilogue { kDequantBf16 = 0, kStoreI32 = 1, kBiasBf16 = 2 };
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
+// Workgroup -> tile. Workgroups go round-robin to the 8 XCDs, so each XCD gets
+// a contiguous range of tiles; m_fast walks the token tiles of one channel
+// panel first (the W panel is then read into one XCD's L2 only), else the
+// channel tiles of one token panel.
+__device__ __forceinline__ void map_tile(int pid, int tiles_m, int tiles_n, bool m_fast, int &tm,
+                                         int &tn) {
+    constexpr int kXcd = 8;
+    const int total = tiles_m * tiles_n;
+    const int full = total - total % kXcd;
+    const int lid = pid < full ? (pid % kXcd) * (full / kXcd) + pid / kXcd : pid;
+    if (m_fast) {
+        tn = lid / tiles_m;
+        tm = lid - tn * tiles_m;
+    } else {
+        tm = lid / tiles_n;
+        tn = lid - tm * tiles_n;
+    }
+}
+
+// W 32-bit words at an address aligned to A bytes. Vector memory instructions
+// take any such address, so rows of an N that is no multiple of 8 go out as
+// vectors too.
+template <int W, int A>
+struct __attribute__((packed, aligned(A))) Words {
+    uint32_t w[W];
+};
+
+// Sums the WK partial tiles in LDS (in order) and writes the tile: quads of 4
+// channels, whole rows per group of lanes; a row's last quad past N element
+// by element. With a 2-byte store per channel where N % 4 != 0 the lanes of a
+// store lay 8 bytes apart: the 128 x 64 tile took 37 us at bf16 3986 x 5214 x
+// 64, with vectors 22.
+template <class Op, int BM, int BN, int RS, int WK, int NT, int EPI>
+__device__ __forceinline__ void reduce_store(const float *red, const float *__restrict__ xs,
+                                             const float *__restrict__ ws,
+                                             const uint16_t *__restrict__ bias, int M, int N,
+                                             int m0, int n0, void *__restrict__ Yout) {
+    for (int q = threadIdx.x; q < BM * BN / 4; q += NT) {
+        const int row = q / (BN / 4), c = (q % (BN / 4)) * 4;
+        typename Op::Acc s = *reinterpret_cast<const typename Op::Acc *>(red + row * RS + c);
+#pragma unroll
+        for (int w = 1; w < WK; ++w)
+            s += *reinterpret_cast<const typename Op::Acc *>(red + (w * BM + row) * RS + c);
+        const int m = m0 + row, n = n0 + c;
+        if (m >= M || n >= N) continue;
+        const int64_t at = static_cast<int64_t>(m) * N + n;
+        const bool whole = n + 4 <= N;
+        if constexpr (EPI == kStoreI32) {
+            int32_t *y = static_cast<int32_t *>(Yout) + at;
+            if (whole) {
+                *reinterpret_cast<Words<4, 4> *>(y) = __builtin_bit_cast(Words<4, 4>, s);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (n + e < N) y[e] = static_cast<int32_t>(s[e]);
+            }
+        } else {
+            float wsc[4] = {0.f, 0.f, 0.f, 0.f};
+            uint32_t b2[2] = {0u, 0u};
+            if (whole) {
+                if constexpr (EPI == kDequantBf16) {
+                    const Words<4, 4> w4 = *reinterpret_cast<const Words<4, 4> *>(ws + n);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) wsc[e] = __uint_as_float(w4.w[e]);
+                }
+                if (bias != nullptr) {
+                    const Words<2, 2> b = *reinterpret_cast<const Words<2, 2> *>(bias + n);
+                    b2[0] = b.w[0];
+                    b2[1] = b.w[1];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    if (n + e >= N) continue;
+                    if constexpr (EPI == kDequantBf16) wsc[e] = ws[n + e];
+                    if (bias != nullptr)
+                        b2[e >> 1] |= static_cast<uint32_t>(bias[n + e]) << (16 * (e & 1));
+                }
+            }
+            float xv = 0.0f;
+            if constexpr (EPI == kDequantBf16) xv = xs[m];
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float a = static_cast<float>(s[e]);
+                const float bb =
+                    __uint_as_float((e & 1) ? (b2[e >> 1] & 0xffff0000u) : (b2[e >> 1] << 16));
+                if constexpr (EPI == kDequantBf16)
+                    y[e] = __builtin_fmaf(a, xv * wsc[e], bb);
+                else
+                    y[e] = a + bb;
+            }
+            uint16_t *o = static_cast<uint16_t *>(Yout) + at;
+            const uint32_t h[2] = {bf16_pair(y[0], y[1]), bf16_pair(y[2], y[3])};
+            if (whole) {
+                *reinterpret_cast<Words<2, 2> *>(o) = Words<2, 2>{{h[0], h[1]}};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (n + e < N) o[e] = static_cast<uint16_t>(h[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+    }
+}
+
+// s_waitcnt with only vmcnt constrained.
+template <int N>
+__device__ __forceinline__ void wait_vmcnt() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
+}
+__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+// Workgroup barrier without a memory fence (which would drain the prefetch);
+// the waits before it order the LDS accesses.
+__device__ __forceinline__ void barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+#define LDS_AS __attribute__((address_space(3)))
+__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, int8_t *lds, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LDS_AS void *)lds, 16, off, 0, 0, 0);
+}
+
+}  // namespace small
+}  // namespace w8a8

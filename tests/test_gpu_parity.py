@@ -275,6 +275,50 @@ def test_every_gemm_configuration(shape, config):
     check_bf16_output(Yb[rows], c["X"].reshape(M, K)[rows], c["W"].reshape(N, K), c["bias"])
 
 
+# Shapes whose weights are decoded inside the GEMM, for each tile of
+# gemm_gguf.hip: ragged tokens and channels, a stage of K that ends past the row
+# (Q8_0), several ring turns, more tiles than CUs.
+GGUF_FUSED = [("q8_0", 1, 1, 64), ("q8_0", 16, 300, 4160), ("q8_0", 31, 4095, 832),
+              ("q8_0", 15, 8190, 1088), ("q8_0", 60, 1000, 2112), ("q8_0", 33, 12001, 448),
+              ("q8_0", 17, 4099, 320), ("q8_0", 17, 9001, 832), ("q8_0", 154, 12287, 320),
+              ("q8_0", 1000, 500, 1024), ("q4_k", 1, 1, 256), ("q4_k", 17, 300, 1024),
+              ("q4_k", 17, 2111, 1024), ("q4_k", 1, 12287, 768), ("q4_k", 16, 8001, 512),
+              ("q4_k", 33, 3001, 1280), ("q4_k", 63, 4099, 2048), ("q4_k", 20, 20001, 256),
+              ("q4_k", 33, 9001, 768), ("q4_k", 128, 8325, 768), ("q4_k", 129, 2111, 1024)]
+
+
+@pytest.mark.parametrize("fmt,M,N,K", GGUF_FUSED)
+def test_gguf_linear_decoded_in_the_gemm(fmt, M, N, K):
+    """Against binary64 products of X with the decode kernel's own weights,
+    within the binary32 summation bound, with and without a bias, between guard
+    bands; `work` is unwritten (the weights never go to memory)."""
+    c = synth.linear_case([150, M, N, K], M, N, K)
+    X, W, b = (dev_bf16(c["X"].reshape(M, K)), dev_bf16(c["W"].reshape(N, K)),
+               dev_bf16(c["bias"]))
+    work = torch.zeros(N, K, dtype=torch.bfloat16, device="cuda")
+    pad = 1024
+    Ybuf = torch.full((M * N + 2 * pad,), 0x1234, dtype=torch.int16, device="cuda")
+    Y = Ybuf[pad:pad + M * N].view(torch.bfloat16).view(M, N)
+    if fmt == "q8_0":
+        qs, d = ops.q8_0_quantize(W)
+        Wd = host_bits(ops.q8_0_dequantize(qs, d))
+    else:
+        q = ops.q4_k_quantize(W)
+        Wd = host_bits(ops.q4_k_dequantize(q))
+    rng = np.random.default_rng([151, M, N, K])
+    rows = np.unique(np.concatenate([[0, M - 1], rng.choice(M, min(M, 60), replace=False)]))
+    for bias in (b, None):
+        if fmt == "q8_0":
+            ops.q8_0_linear(X, qs, d, bias, work=work, out=Y)
+        else:
+            ops.q4_k_linear(X, q, bias, work=work, out=Y)
+        check_bf16_output(host_bits(Y)[rows], c["X"].reshape(M, K)[rows], Wd,
+                          c["bias"] if bias is not None else None)
+    assert not bool(work.any())
+    g = host(Ybuf)
+    assert np.all(g[:pad] == 0x1234) and np.all(g[pad + M * N:] == 0x1234)
+
+
 # Shapes that the small tiles take (gemm_small.hip): for each tile its edges
 # (one row or channel less, equal, one more), N odd and N % 4 == 0, K from one
 # 64-byte step to several ring turns with a half K tile left over, and outputs
