@@ -80,6 +80,7 @@ class Workspace:
         self._xq = None
         self._xs = None
         self._wd = None
+        self._views = None  # (M, K, Xq, x_scale) of the last get()
 
     def weights(self, N: int, K: int) -> torch.Tensor:
         if self._wd is None or self._wd.numel() < N * K:
@@ -87,12 +88,16 @@ class Workspace:
         return self._wd[: N * K].view(N, K)
 
     def get(self, M: int, K: int):
+        v = self._views
+        if v is not None and v[0] == M and v[1] == K:
+            return v[2], v[3]
         need = M * K
         if self._xq is None or self._xq.numel() < need:
             self._xq = torch.empty(need, dtype=torch.int8, device=self.device)
         if self._xs is None or self._xs.numel() < M:
             self._xs = torch.empty(M, dtype=torch.float32, device=self.device)
-        return self._xq[:need].view(M, K), self._xs[:M]
+        v = self._views = (M, K, self._xq[:need].view(M, K), self._xs[:M])
+        return v[2], v[3]
 
 
 def route(layer: PreparedLinear, X: torch.Tensor, out: torch.Tensor | None = None,

@@ -19,8 +19,23 @@ __all__ = [
 ]
 
 
-def _stream(device: torch.device) -> int:
-    return torch.cuda.current_stream(device).cuda_stream
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
+def _launch(name: str, device: torch.device, *args) -> None:
+    """Calls an entry point with torch's current stream of `device` and raises
+    on a non-zero status. The device is switched only where another one is
+    current: with small layers the Python around a launch is most of a call,
+    and the context manager and a Stream object cost several us of it."""
+    fn = getattr(load(), name)
+    i = device.index
+    if torch.cuda.current_device() == i:
+        status = fn(*args, _raw_stream(i))
+    else:
+        with torch.cuda.device(device):
+            status = fn(*args, _raw_stream(i))
+    if status:
+        check(name, status)
 
 
 def _ptr(t):
@@ -28,6 +43,9 @@ def _ptr(t):
 
 
 def _need(t: torch.Tensor, name: str, dtype: torch.dtype, ndim: int, device=None) -> torch.Tensor:
+    if (isinstance(t, torch.Tensor) and t.dtype is dtype and t.dim() == ndim and t.is_cuda
+            and t.is_contiguous() and (device is None or t.device == device)):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -38,9 +56,7 @@ def _need(t: torch.Tensor, name: str, dtype: torch.dtype, ndim: int, device=None
         raise ValueError(f"{name} must be on a GPU, got {t.device}")
     if device is not None and t.device != device:
         raise ValueError(f"{name} is on {t.device}, expected {device}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t
+    raise ValueError(f"{name} must be contiguous")
 
 
 def _need_vec(t: torch.Tensor, name: str, dtype: torch.dtype, n: int, device=None) -> torch.Tensor:
@@ -56,7 +72,7 @@ def _out(t, shape, dtype, device, name):
     if t is None:
         return torch.empty(shape, dtype=dtype, device=device)
     _need(t, name, dtype, len(shape), device)
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
     return t
 
@@ -66,10 +82,7 @@ def w8a8_act_absmax(X: torch.Tensor, absmax: torch.Tensor) -> torch.Tensor:
     _need(X, "X", torch.bfloat16, 2)
     M, K = X.shape
     _need_vec(absmax, "absmax", torch.float32, K, X.device)
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("w8a8_act_absmax",
-              lib.w8a8_act_absmax(_ptr(X), M, K, _ptr(absmax), _stream(X.device)))
+    _launch("w8a8_act_absmax", X.device, _ptr(X), M, K, _ptr(absmax))
     return absmax
 
 
@@ -86,10 +99,7 @@ def w8a8_act_moments(X: torch.Tensor, work: torch.Tensor | None = None,
     _need(work, "work", torch.uint8, 1, X.device)
     if work.numel() < MOMENTS_WORK_BYTES:
         raise ValueError(f"work needs {MOMENTS_WORK_BYTES} bytes")
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("w8a8_act_moments",
-              lib.w8a8_act_moments(_ptr(X), M, K, _ptr(work), _ptr(stats), _stream(X.device)))
+    _launch("w8a8_act_moments", X.device, _ptr(X), M, K, _ptr(work), _ptr(stats))
     return stats
 
 
@@ -100,10 +110,7 @@ def w8a8_act_moments_noalloc(X: torch.Tensor, out: torch.Tensor) -> torch.Tensor
     _need(X, "X", torch.bfloat16, 2)
     M, K = X.shape
     stats = _out(out, (4,), torch.float64, X.device, "out")
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("w8a8_act_moments_noalloc",
-              lib.w8a8_act_moments_noalloc(_ptr(X), M, K, _ptr(stats), _stream(X.device)))
+    _launch("w8a8_act_moments_noalloc", X.device, _ptr(X), M, K, _ptr(stats))
     return stats
 
 
@@ -114,11 +121,8 @@ def w8a8_smooth_factors(act_absmax: torch.Tensor, W: torch.Tensor, alpha: float 
     N, K = W.shape
     _need_vec(act_absmax, "act_absmax", torch.float32, K, W.device)
     lam = _out(out, (K,), torch.float32, W.device, "out")
-    lib = load()
-    with torch.cuda.device(W.device):
-        check("w8a8_smooth_factors",
-              lib.w8a8_smooth_factors(_ptr(act_absmax), _ptr(W), N, K, float(alpha), _ptr(lam),
-                                      _stream(W.device)))
+    _launch("w8a8_smooth_factors", W.device, _ptr(act_absmax), _ptr(W), N, K, float(alpha),
+            _ptr(lam))
     return lam
 
 
@@ -132,11 +136,8 @@ def w8a8_prepare_weight(W: torch.Tensor, lam: torch.Tensor, Wq=None, w_scale=Non
     Wq = _out(Wq, (N, K), torch.int8, dev, "Wq")
     w_scale = _out(w_scale, (N,), torch.float32, dev, "w_scale")
     inv_lambda = _out(inv_lambda, (K,), torch.float32, dev, "inv_lambda")
-    lib = load()
-    with torch.cuda.device(dev):
-        check("w8a8_prepare_weight",
-              lib.w8a8_prepare_weight(_ptr(W), _ptr(lam), N, K, _ptr(Wq), _ptr(w_scale),
-                                      _ptr(inv_lambda), _stream(dev)))
+    _launch("w8a8_prepare_weight", dev, _ptr(W), _ptr(lam), N, K, _ptr(Wq), _ptr(w_scale),
+            _ptr(inv_lambda))
     return Wq, w_scale, inv_lambda
 
 
@@ -148,11 +149,7 @@ def w8a8_quant_act(X: torch.Tensor, inv_lambda: torch.Tensor, Xq=None, x_scale=N
     dev = X.device
     Xq = _out(Xq, (M, K), torch.int8, dev, "Xq")
     x_scale = _out(x_scale, (M,), torch.float32, dev, "x_scale")
-    lib = load()
-    with torch.cuda.device(dev):
-        check("w8a8_quant_act",
-              lib.w8a8_quant_act(_ptr(X), _ptr(inv_lambda), M, K, _ptr(Xq), _ptr(x_scale),
-                                 _stream(dev)))
+    _launch("w8a8_quant_act", dev, _ptr(X), _ptr(inv_lambda), M, K, _ptr(Xq), _ptr(x_scale))
     return Xq, x_scale
 
 
@@ -168,11 +165,8 @@ def w8a8_adaln_quant_act(X: torch.Tensor, shift: torch.Tensor, scale: torch.Tens
     _need_vec(inv_lambda, "inv_lambda", torch.float32, K, dev)
     Xq = _out(Xq, (M, K), torch.int8, dev, "Xq")
     x_scale = _out(x_scale, (M,), torch.float32, dev, "x_scale")
-    lib = load()
-    with torch.cuda.device(dev):
-        check("w8a8_adaln_quant_act",
-              lib.w8a8_adaln_quant_act(_ptr(X), _ptr(shift), _ptr(scale), _ptr(inv_lambda), M, K,
-                                       float(eps), _ptr(Xq), _ptr(x_scale), _stream(dev)))
+    _launch("w8a8_adaln_quant_act", dev, _ptr(X), _ptr(shift), _ptr(scale), _ptr(inv_lambda), M,
+            K, float(eps), _ptr(Xq), _ptr(x_scale))
     return Xq, x_scale
 
 
@@ -191,11 +185,8 @@ def w8a8_linear(Xq: torch.Tensor, x_scale: torch.Tensor, Wq: torch.Tensor,
     if bias is not None:
         _need_vec(bias, "bias", torch.bfloat16, N, Xq.device)
     Y = _out(out, (M, N), torch.bfloat16, Xq.device, "out")
-    lib = load()
-    with torch.cuda.device(Xq.device):
-        check("w8a8_linear",
-              lib.w8a8_linear(_ptr(Xq), _ptr(x_scale), _ptr(Wq), _ptr(w_scale), _ptr(bias),
-                              M, N, K, _ptr(Y), _stream(Xq.device)))
+    _launch("w8a8_linear", Xq.device, _ptr(Xq), _ptr(x_scale), _ptr(Wq), _ptr(w_scale),
+            _ptr(bias), M, N, K, _ptr(Y))
     return Y
 
 
@@ -208,10 +199,7 @@ def w8a8_gemm_i32(Xq: torch.Tensor, Wq: torch.Tensor, out: torch.Tensor | None =
     if Wq.shape[1] != K:
         raise ValueError("Xq and Wq must share K")
     C = _out(out, (M, N), torch.int32, Xq.device, "out")
-    lib = load()
-    with torch.cuda.device(Xq.device):
-        check("w8a8_gemm_i32",
-              lib.w8a8_gemm_i32(_ptr(Xq), _ptr(Wq), M, N, K, _ptr(C), _stream(Xq.device)))
+    _launch("w8a8_gemm_i32", Xq.device, _ptr(Xq), _ptr(Wq), M, N, K, _ptr(C))
     return C
 
 
@@ -227,10 +215,7 @@ def bf16_linear(X: torch.Tensor, W: torch.Tensor, bias: torch.Tensor | None = No
     if bias is not None:
         _need_vec(bias, "bias", torch.bfloat16, N, X.device)
     Y = _out(out, (M, N), torch.bfloat16, X.device, "out")
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("bf16_linear",
-              lib.bf16_linear(_ptr(X), _ptr(W), _ptr(bias), M, N, K, _ptr(Y), _stream(X.device)))
+    _launch("bf16_linear", X.device, _ptr(X), _ptr(W), _ptr(bias), M, N, K, _ptr(Y))
     return Y
 
 
@@ -256,10 +241,7 @@ def q8_0_quantize(W: torch.Tensor) -> tuple[torch.Tensor, torch.Tensor]:
     N, K = W.shape
     qs = torch.empty(N, K, dtype=torch.int8, device=W.device)
     d = torch.empty(N, K // Q8_0_BLOCK, dtype=torch.float16, device=W.device)
-    lib = load()
-    with torch.cuda.device(W.device):
-        check("q8_0_quantize", lib.q8_0_quantize(_ptr(W), N, K, _ptr(qs), _ptr(d),
-                                                 _stream(W.device)))
+    _launch("q8_0_quantize", W.device, _ptr(W), N, K, _ptr(qs), _ptr(d))
     return qs, d
 
 
@@ -272,10 +254,7 @@ def q8_0_dequantize(qs: torch.Tensor, d: torch.Tensor,
     if tuple(d.shape) != (N, K // Q8_0_BLOCK):
         raise ValueError("d must be [N, K/32]")
     W = _out(out, (N, K), torch.bfloat16, qs.device, "out")
-    lib = load()
-    with torch.cuda.device(qs.device):
-        check("q8_0_dequantize", lib.q8_0_dequantize(_ptr(qs), _ptr(d), N, K, _ptr(W),
-                                                     _stream(qs.device)))
+    _launch("q8_0_dequantize", qs.device, _ptr(qs), _ptr(d), N, K, _ptr(W))
     return W
 
 
@@ -297,10 +276,8 @@ def q8_0_linear(X: torch.Tensor, qs: torch.Tensor, d: torch.Tensor,
         _need_vec(bias, "bias", torch.bfloat16, N, X.device)
     work = _out(work, (N, K), torch.bfloat16, X.device, "work")
     Y = _out(out, (M, N), torch.bfloat16, X.device, "out")
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("q8_0_linear", lib.q8_0_linear(_ptr(X), _ptr(qs), _ptr(d), _ptr(bias), M, N, K,
-                                             _ptr(work), _ptr(Y), _stream(X.device)))
+    _launch("q8_0_linear", X.device, _ptr(X), _ptr(qs), _ptr(d), _ptr(bias), M, N, K, _ptr(work),
+            _ptr(Y))
     return Y
 
 
@@ -356,9 +333,7 @@ def q4_k_quantize(W: torch.Tensor) -> Q4K:
             torch.empty(N, K // Q4_K_SUPER * 12, dtype=torch.uint8, device=dev),
             torch.empty(N, K // Q4_K_SUPER, dtype=torch.float16, device=dev),
             torch.empty(N, K // Q4_K_SUPER, dtype=torch.float16, device=dev))
-    lib = load()
-    with torch.cuda.device(dev):
-        check("q4_k_quantize", lib.q4_k_quantize(_ptr(W), N, K, *q.ptrs(), _stream(dev)))
+    _launch("q4_k_quantize", dev, _ptr(W), N, K, *q.ptrs())
     return q
 
 
@@ -367,9 +342,7 @@ def q4_k_dequantize(q: Q4K, out: torch.Tensor | None = None) -> torch.Tensor:
     N, K = q.check()
     dev = q.qs.device
     W = _out(out, (N, K), torch.bfloat16, dev, "out")
-    lib = load()
-    with torch.cuda.device(dev):
-        check("q4_k_dequantize", lib.q4_k_dequantize(*q.ptrs(), N, K, _ptr(W), _stream(dev)))
+    _launch("q4_k_dequantize", dev, *q.ptrs(), N, K, _ptr(W))
     return W
 
 
@@ -386,8 +359,5 @@ def q4_k_linear(X: torch.Tensor, q: Q4K, bias: torch.Tensor | None = None,
         _need_vec(bias, "bias", torch.bfloat16, N, X.device)
     work = _out(work, (N, K), torch.bfloat16, X.device, "work")
     Y = _out(out, (M, N), torch.bfloat16, X.device, "out")
-    lib = load()
-    with torch.cuda.device(X.device):
-        check("q4_k_linear", lib.q4_k_linear(_ptr(X), *q.ptrs(), _ptr(bias), M, N, K,
-                                             _ptr(work), _ptr(Y), _stream(X.device)))
+    _launch("q4_k_linear", X.device, _ptr(X), *q.ptrs(), _ptr(bias), M, N, K, _ptr(work), _ptr(Y))
     return Y
