@@ -3,17 +3,25 @@
 // deviation and Pearson kurtosis m4 / m2^2 over all entries of X, in binary64.
 //
 // One pass over X. A fixed grid of kMomentBlocks workgroups walks X in
-// 16-byte chunks (8 entries) with a fixed stride; each thread takes its
-// chunks kUnroll at a time (the loads first). For such a group of up to 32
-// entries it computes the group's own mean and central sums of the second,
-// third and fourth powers around it, from registers, and merges them into
-// its running state with the pairwise update for central moments (Chan,
-// Golub and LeVeque for the second; Pebay, 2008, for the third and fourth).
-// Sums are never taken of raw powers, which would cancel. The threads'
-// states merge in a fixed tree in LDS and each workgroup writes its state to
-// the caller's workspace; one workgroup then merges the kMomentBlocks states
-// in a fixed tree. Every call on the same input therefore returns the same
-// bits, and X is read once, nontemporally.
+// 16-byte chunks (8 entries) with a fixed stride. A workgroup takes kUnroll
+// chunks per thread into registers (the loads first), adds them up for the
+// mean of all those entries, then takes the central sums of the second, third
+// and fourth powers around it from the same registers: one exchange of one
+// sum and one of three per 24576 entries. Longer inputs take several such
+// rounds, merged with the pairwise update for central moments (Chan, Golub and
+// LeVeque for the second; Pebay, 2008, for the third and fourth). Sums are
+// never taken of raw powers, which would cancel. Each workgroup writes its
+// state to the caller's workspace; one workgroup then forms the mean of all
+// entries from the kMomentBlocks means and moves every state's central sums to
+// it (exact identities), so that they add. Every order is fixed: calls on the
+// same input return the same bits, and X is read once, nontemporally.
+//
+// Bound by issue: eight binary64 operations per entry, two of them
+// conversions. At 4608 x 4096 (37.7 MB) the pass takes 14.4 us and the merge
+// 2.7; with a mean per thread and group of 32 entries, merged pairwise over the
+// threads in a tree of LDS steps, they took 16.2 and 5.0. (Rounds of four
+// chunks with the next ones in flight, around a pivot instead of the mean, took
+// as long: the reads are not what it waits for.)
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -22,6 +30,7 @@
 #include <mutex>
 
 #include "internal.h"
+#include "wave_reduce.h"
 
 // Workgroup states of w8a8_act_moments_noalloc, for callers that cannot
 // allocate: one file-scope device array instead of a caller workspace. Each
@@ -33,7 +42,8 @@ namespace w8a8 {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kUnroll = 4;      // chunk loads in flight per thread
+constexpr int kWaves = kThreads / 64;
+constexpr int kUnroll = 12;     // chunks per thread and round, all in flight
 constexpr int kStateWords = 6;  // n, mean, M2, M3, M4, max |x| (binary64 each)
 
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
@@ -79,40 +89,6 @@ __device__ __forceinline__ Moments merge(const Moments &a, const Moments &b) {
     return r;
 }
 
-__device__ __forceinline__ void put(double *s, int i, const Moments &m) {
-    s[5 * i] = m.n;
-    s[5 * i + 1] = m.mean;
-    s[5 * i + 2] = m.m2;
-    s[5 * i + 3] = m.m3;
-    s[5 * i + 4] = m.m4;
-}
-
-__device__ __forceinline__ Moments get(const double *s, int i) {
-    return Moments{s[5 * i], s[5 * i + 1], s[5 * i + 2], s[5 * i + 3], s[5 * i + 4]};
-}
-
-// Merges the NT threads' states (and maxima) of a workgroup in a fixed tree:
-// at each level thread t < h takes thread t + h's state. Valid in thread 0.
-// (Lane shuffles instead of LDS for the levels inside a wave measured
-// slower: every lane of a wave then runs each level's merge.)
-template <int NT>
-__device__ __forceinline__ Moments group_merge(Moments m, float &mx, double *s, float *smx) {
-    put(s, threadIdx.x, m);
-    smx[threadIdx.x] = mx;
-    __syncthreads();
-#pragma unroll 1
-    for (int h = NT / 2; h > 0; h >>= 1) {
-        if (static_cast<int>(threadIdx.x) < h) {
-            m = merge(m, get(s, threadIdx.x + h));
-            mx = fmaxf(mx, smx[threadIdx.x + h]);
-            put(s, threadIdx.x, m);
-            smx[threadIdx.x] = mx;
-        }
-        __syncthreads();
-    }
-    return m;
-}
-
 // The 8 entries of a chunk, widened (exactly).
 __device__ __forceinline__ void widen8(const uint4 &x, float (&v)[8]) {
     v[0] = lo(x.x);
@@ -125,64 +101,102 @@ __device__ __forceinline__ void widen8(const uint4 &x, float (&v)[8]) {
     v[7] = hi(x.w);
 }
 
-// Pass over X: thread t of the grid takes chunks t, t + stride, ... in
-// groups of kUnroll; workgroup b writes its merged state and max |x| to
+// Pass over X: in a round, thread t of workgroup b takes chunks base + t + u
+// stride (u < kUnroll); the workgroup writes its state and max |x| to
 // part[kStateWords b ...].
 __global__ __launch_bounds__(kThreads) void moments_pass_kernel(const uint4 *__restrict__ X,
                                                                 int64_t chunks,
                                                                 double *__restrict__ part) {
-    __shared__ double s[5 * kThreads];
-    __shared__ float smx[kThreads];
+    __shared__ double s1[kWaves];
+    __shared__ double s234[kWaves][3];
+    __shared__ float smx[kWaves];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
     Moments st{0.0, 0.0, 0.0, 0.0, 0.0};
     float mx = 0.0f;
-    for (int64_t c0 = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; c0 < chunks;
-         c0 += kUnroll * stride) {
+    for (int64_t base = static_cast<int64_t>(blockIdx.x) * kThreads; base < chunks;
+         base += kUnroll * stride) {
         uint4 x[kUnroll];
+        int valid = 0;  // chunks of this thread (the first ones)
+        int64_t wg = 0;  // chunks of the workgroup
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const int64_t c = c0 + u * stride;
-            x[u] = c < chunks ? load_stream(X + c) : make_uint4(0u, 0u, 0u, 0u);
+            const int64_t c = base + u * stride;
+            const bool in = c + threadIdx.x < chunks;
+            x[u] = in ? load_stream(X + c + threadIdx.x) : make_uint4(0u, 0u, 0u, 0u);
+            valid += in ? 1 : 0;
+            const int64_t left = chunks - c;
+            wg += left < 0 ? 0 : left < kThreads ? left : kThreads;
         }
-        int valid = 0;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) valid += c0 + u * stride < chunks ? 1 : 0;
-        // the group's mean (its entries are exact in binary64; 8 valid ones
-        // per chunk, and zero-filled chunks add nothing to the sum)
-        double dv[kUnroll][8];
-        double sum = 0.0;
+        // the mean of the workgroup's entries (exact in binary64; zero-filled
+        // chunks add nothing)
+        double a0 = 0.0, a1 = 0.0;
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (u >= valid) continue;
+            float v[8];
+            widen8(x[u], v);
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                a0 += static_cast<double>(v[e]);
+                a1 += static_cast<double>(v[e + 1]);
+                mx = fmaxf(mx, fmaxf(fabsf(v[e]), fabsf(v[e + 1])));
+            }
+        }
+        const double sum = lanes::sum(a0 + a1);
+        if (lane == 0) s1[wave] = sum;
+        __syncthreads();
+        double total = s1[0];
+#pragma unroll
+        for (int w = 1; w < kWaves; ++w) total += s1[w];
+        const double cnt = 8.0 * static_cast<double>(wg);
+        const double mean = total / cnt;
+        // central sums around it; the third and fourth powers accumulate with
+        // fused multiply-adds (one rounding each). The entries are widened again
+        // (opaque copies): kept as binary64 across the exchange they would take
+        // 192 registers and leave half the waves.
+        double g2 = 0.0, g3 = 0.0, g4 = 0.0;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            if (u >= valid) continue;
+            asm volatile("" : "+v"(x[u].x), "+v"(x[u].y), "+v"(x[u].z), "+v"(x[u].w));
             float v[8];
             widen8(x[u], v);
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                dv[u][e] = static_cast<double>(v[e]);
-                sum += dv[u][e];
-                mx = fmaxf(mx, fabsf(v[e]));
-            }
-        }
-        const double cnt = 8.0 * valid;
-        const double gm = valid == kUnroll ? sum * (1.0 / (8.0 * kUnroll)) : sum / cnt;
-        // central sums around it; the third and fourth powers accumulate
-        // with fused multiply-adds (one rounding each)
-        double g2 = 0.0, g3 = 0.0, g4 = 0.0;
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            if (u >= valid) break;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const double d = dv[u][e] - gm;
+                const double d = static_cast<double>(v[e]) - mean;
                 const double d2 = d * d;
                 g2 += d2;
                 g3 = __builtin_fma(d2, d, g3);
                 g4 = __builtin_fma(d2, d2, g4);
             }
         }
-        st = merge(st, Moments{cnt, gm, g2, g3, g4});
+        g2 = lanes::sum(g2);
+        g3 = lanes::sum(g3);
+        g4 = lanes::sum(g4);
+        if (lane == 0) {
+            s234[wave][0] = g2;
+            s234[wave][1] = g3;
+            s234[wave][2] = g4;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            Moments r{cnt, mean, s234[0][0], s234[0][1], s234[0][2]};
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) {
+                r.m2 += s234[w][0];
+                r.m3 += s234[w][1];
+                r.m4 += s234[w][2];
+            }
+            st = merge(st, r);
+        }
     }
-    st = group_merge<kThreads>(st, mx, s, smx);
+    mx = lanes::max_nonneg(mx);
+    if (lane == 0) smx[wave] = mx;
+    __syncthreads();
     if (threadIdx.x == 0) {
+        for (int w = 1; w < kWaves; ++w) mx = fmaxf(mx, smx[w]);
         double *o = part + kStateWords * blockIdx.x;
         o[0] = st.n;
         o[1] = st.mean;
@@ -194,22 +208,54 @@ __global__ __launch_bounds__(kThreads) void moments_pass_kernel(const uint4 *__r
 }
 
 // stats = [max |x|, mean, sqrt(m2), m4 / m2^2 (0 when m2 == 0)] from the
-// kMomentBlocks workgroup states, merged in a fixed tree.
+// kMomentBlocks workgroup states: with delta = a state's mean - the mean, its
+// sums around the mean are m2 + n delta^2, m3 + delta (3 m2 + n delta^2) and
+// m4 + delta (4 m3 + delta (6 m2 + n delta^2)).
 __global__ __launch_bounds__(kMomentBlocks) void moments_final_kernel(
-    const double *__restrict__ part, double *__restrict__ stats) {
-    __shared__ double s[5 * kMomentBlocks];
-    __shared__ float smx[kMomentBlocks];
+    const double *__restrict__ part, double n, double *__restrict__ stats) {
+    constexpr int kW = kMomentBlocks / 64;
+    __shared__ double s1[kW];
+    __shared__ double s24[kW][2];
+    __shared__ float smx[kW];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
     const double *p = part + kStateWords * threadIdx.x;
-    Moments m{p[0], p[1], p[2], p[3], p[4]};
-    float mx = static_cast<float>(p[5]);
-    m = group_merge<kMomentBlocks>(m, mx, s, smx);
+    const Moments m{p[0], p[1], p[2], p[3], p[4]};
+    const float mx = lanes::max_nonneg(static_cast<float>(p[5]));
+    const double sum = lanes::sum(m.n * m.mean);
+    if (lane == 0) {
+        s1[wave] = sum;
+        smx[wave] = mx;
+    }
+    __syncthreads();
+    double total = s1[0];
+#pragma unroll
+    for (int w = 1; w < kW; ++w) total += s1[w];
+    const double mean = total / n;
+    const double d = m.mean - mean;
+    const double nd2 = m.n * d * d;
+    const double m2 = lanes::sum(m.m2 + nd2);
+    const double m4 = lanes::sum(m.m4 + d * (4.0 * m.m3 + d * (6.0 * m.m2 + nd2)));
+    if (lane == 0) {
+        s24[wave][0] = m2;
+        s24[wave][1] = m4;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-        const double m2 = m.m2 / m.n;
-        const double m4 = m.m4 / m.n;
-        stats[0] = static_cast<double>(mx);
-        stats[1] = m.mean;
-        stats[2] = sqrt(m2);
-        stats[3] = m2 > 0.0 ? m4 / (m2 * m2) : 0.0;
+        double t2 = s24[0][0], t4 = s24[0][1];
+        float t0 = smx[0];
+#pragma unroll
+        for (int w = 1; w < kW; ++w) {
+            t2 += s24[w][0];
+            t4 += s24[w][1];
+            t0 = fmaxf(t0, smx[w]);
+        }
+        t2 /= n;
+        t4 /= n;
+        stats[0] = static_cast<double>(t0);
+        stats[1] = mean;
+        stats[2] = sqrt(t2);
+        stats[3] = t2 > 0.0 ? t4 / (t2 * t2) : 0.0;
     }
 }
 
@@ -265,7 +311,7 @@ hipError_t launch_act_moments(const uint16_t *X, int64_t n, double *work, double
     hipLaunchKernelGGL(moments_pass_kernel, dim3(kMomentBlocks), dim3(kThreads), 0, stream,
                        reinterpret_cast<const uint4 *>(X), chunks, work);
     hipLaunchKernelGGL(moments_final_kernel, dim3(1), dim3(kMomentBlocks), 0, stream, work,
-                       stats);
+                       static_cast<double>(n), stats);
     return hipGetLastError();
 }
 
