@@ -169,9 +169,8 @@ w8a8_status w8a8_prepare_weight(const uint16_t *W, const float *lambda, int64_t 
         return W8A8_ERR_ALIGN;
     W8A8_TRY(check_alias({{Wq, N * K}, {w_scale, 4 * N}, {inv_lambda, 4 * K}},
                          {{W, 2 * N * K}, {lambda, 4 * K}}));
-    const hipStream_t s = as_stream(stream);
-    W8A8_TRY(hip_status(w8a8::launch_reciprocal(lambda, K, inv_lambda, s)));
-    return hip_status(w8a8::launch_smooth_quant_rows(W, lambda, N, K, Wq, w_scale, s));
+    return hip_status(w8a8::launch_smooth_quant_rows(W, lambda, N, K, Wq, w_scale, inv_lambda,
+                                                     as_stream(stream)));
 }
 
 w8a8_status w8a8_quant_act(const uint16_t *X, const float *inv_lambda, int64_t M, int64_t K,
@@ -186,7 +185,8 @@ w8a8_status w8a8_quant_act(const uint16_t *X, const float *inv_lambda, int64_t M
     W8A8_TRY(check_alias({{Xq, M * K}, {x_scale, 4 * M}}, {{X, 2 * M * K}, {inv_lambda, 4 * K}}));
     if (M == 0) return W8A8_OK;
     return hip_status(
-        w8a8::launch_smooth_quant_rows(X, inv_lambda, M, K, Xq, x_scale, as_stream(stream)));
+        w8a8::launch_smooth_quant_rows(X, inv_lambda, M, K, Xq, x_scale, nullptr,
+                                       as_stream(stream)));
 }
 
 w8a8_status w8a8_adaln_quant_act(const uint16_t *X, const uint16_t *shift, const uint16_t *scale,

@@ -11,13 +11,10 @@ namespace w8a8 {
 // Smoothing + per-row symmetric INT8 quantization of R rows of K bf16
 // values: out[r][k] = clamp(rint((src[r][k] * mul[k]) * RN(127/absmax_r))),
 // scale[r] = absmax_r / 127 (0 and all-zero codes below the tiny threshold).
+// inv (4-byte aligned, or NULL): inv[k] = RN(1 / mul[k]) besides.
 hipError_t launch_smooth_quant_rows(const uint16_t *src, const float *mul,
                                     int64_t R, int64_t K, int8_t *out,
-                                    float *scale, hipStream_t stream);
-
-// inv[k] = RN(1 / lam[k]).
-hipError_t launch_reciprocal(const float *lam, int64_t K, float *inv,
-                             hipStream_t stream);
+                                    float *scale, float *inv, hipStream_t stream);
 
 // colmax[k] = max(colmax[k], max_r |src[r][k]|) over R rows of bf16.
 hipError_t launch_col_absmax(const uint16_t *src, int64_t R, int64_t K,

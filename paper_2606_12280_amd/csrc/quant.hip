@@ -1,7 +1,6 @@
 // Memory-bound kernels of the W8A8 recipe (paper Section 3, "INT8 W8A8"):
 //   - smooth + per-row INT8 quantization (activations per token at run time,
 //     weights per output channel offline);
-//   - the reciprocal of the smoothing factors;
 //   - calibration: per-channel absmax and the smoothing equation
 //     lambda_j = s_j^alpha / max_i |W_ij|^(1-alpha).
 //
@@ -69,7 +68,8 @@ __device__ __forceinline__ float absmax8(const uint4 &x, const float4 &ma, const
 template <int G, int CH, int WPB, bool PF>
 __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
     const uint16_t *__restrict__ src, const float *__restrict__ mul, int64_t R,
-    int64_t K, int rows_per_group, int8_t *__restrict__ out, float *__restrict__ scale) {
+    int64_t K, int rows_per_group, int8_t *__restrict__ out, float *__restrict__ scale,
+    float *__restrict__ inv) {
     constexpr int SLOTS = WPB / G;
     static_assert(SLOTS * G == WPB, "G must divide WPB");
     __shared__ float red[2][SLOTS][G];
@@ -92,6 +92,19 @@ __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
         const bool live = col(c) < nchunk;
         ma[c] = live ? m4[2 * col(c)] : make_float4(0.f, 0.f, 0.f, 0.f);
         mb[c] = live ? m4[2 * col(c) + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (inv != nullptr && group == 0) {
+        // inv need only be 4-byte aligned
+        struct __attribute__((packed, aligned(4))) Eight {
+            float v[8];
+        };
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (col(c) >= nchunk) continue;
+            *reinterpret_cast<Eight *>(inv + 8 * static_cast<size_t>(col(c))) =
+                Eight{{1.0f / ma[c].x, 1.0f / ma[c].y, 1.0f / ma[c].z, 1.0f / ma[c].w,
+                       1.0f / mb[c].x, 1.0f / mb[c].y, 1.0f / mb[c].z, 1.0f / mb[c].w}};
+        }
     }
     const uint32_t scale_off = (gw == 0 && lane == 0) ? 0u : 4u;
     // the rows' resources: K bf16 in, K codes out, one scale out; empty past
@@ -190,7 +203,7 @@ __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
 // inputs), each walking an equal share of the rows.
 template <int G, int CH, int WPB, bool PF>
 hipError_t launch_rows(const uint16_t *src, const float *mul, int64_t R, int64_t K,
-                       int8_t *out, float *scale, hipStream_t stream) {
+                       int8_t *out, float *scale, float *inv, hipStream_t stream) {
     constexpr int SLOTS = WPB / G;
     if (R <= 0) return hipSuccess;
     static std::atomic<int64_t> resident[256];
@@ -209,14 +222,8 @@ hipError_t launch_rows(const uint16_t *src, const float *mul, int64_t R, int64_t
     if (blocks * WPB * 64 >= (INT64_C(1) << 32)) return hipErrorInvalidValue;
     hipLaunchKernelGGL((smooth_quant_rows_kernel<G, CH, WPB, PF>),
                        dim3(static_cast<unsigned>(blocks)), dim3(WPB * 64), 0, stream, src, mul,
-                       R, K, static_cast<int>(rpg), out, scale);
+                       R, K, static_cast<int>(rpg), out, scale, inv);
     return hipGetLastError();
-}
-
-__global__ void reciprocal_kernel(const float *__restrict__ lam, int64_t K,
-                                  float *__restrict__ inv) {
-    const int64_t k = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (k < K) inv[k] = 1.0f / lam[k];
 }
 
 __global__ void zero_kernel(float *__restrict__ dst, int64_t K) {
@@ -316,23 +323,17 @@ unsigned blocks_for(int64_t n, int threads) {
 }  // namespace
 
 hipError_t launch_smooth_quant_rows(const uint16_t *src, const float *mul, int64_t R,
-                                    int64_t K, int8_t *out, float *scale,
+                                    int64_t K, int8_t *out, float *scale, float *inv,
                                     hipStream_t stream) {
     // A group covers 512 * G * CH columns; take the smallest that holds K.
-    if (K <= 512) return launch_rows<1, 1, 4, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 1024) return launch_rows<2, 1, 4, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 2048) return launch_rows<4, 1, 4, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 4096) return launch_rows<4, 2, 4, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 8192) return launch_rows<8, 2, 8, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 16384) return launch_rows<8, 4, 8, true>(src, mul, R, K, out, scale, stream);
-    if (K <= 32768) return launch_rows<8, 8, 8, true>(src, mul, R, K, out, scale, stream);
-    return launch_rows<16, 8, 16, false>(src, mul, R, K, out, scale, stream);  // K <= 65536
-}
-
-hipError_t launch_reciprocal(const float *lam, int64_t K, float *inv, hipStream_t stream) {
-    hipLaunchKernelGGL(reciprocal_kernel, dim3(blocks_for(K, 256)), dim3(256), 0, stream, lam,
-                       K, inv);
-    return hipGetLastError();
+    if (K <= 512) return launch_rows<1, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 1024) return launch_rows<2, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 2048) return launch_rows<4, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 4096) return launch_rows<4, 2, 4, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 8192) return launch_rows<8, 2, 8, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 16384) return launch_rows<8, 4, 8, true>(src, mul, R, K, out, scale, inv, stream);
+    if (K <= 32768) return launch_rows<8, 8, 8, true>(src, mul, R, K, out, scale, inv, stream);
+    return launch_rows<16, 8, 16, false>(src, mul, R, K, out, scale, inv, stream);  // K <= 65536
 }
 
 hipError_t launch_zero_f32(float *dst, int64_t K, hipStream_t stream) {
