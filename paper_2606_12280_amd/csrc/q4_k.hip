@@ -163,7 +163,9 @@ __global__ __launch_bounds__(256) void q4_k_quantize_kernel(
 // each half of the wave takes its own. That leaves three vector loads per
 // thread instead of six (36.1 -> 33.4 us at 16384 x 4096 in one job, output
 // identical). The second super-block is clamped to the last one, so a wave
-// whose upper half lies past the end reads nothing outside the planes.
+// whose upper half lies past the end reads nothing outside the planes. The
+// weights are stored without a nontemporal hint: the GEMM that follows reads
+// them (see q8_0_dequantize_kernel).
 __global__ __launch_bounds__(256) void q4_k_dequantize_kernel(
     const uint32_t *__restrict__ qs, const uint32_t *__restrict__ scales,
     const uint16_t *__restrict__ d, const uint16_t *__restrict__ dmin, int64_t octets,
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(256) void q4_k_dequantize_kernel(
         const float q1 = static_cast<float>((q >> (8 * e + 4)) & 15u);
         out[e] = bf16_pair(s * q0 - o, s * q1 - o);
     }
-    __builtin_nontemporal_store(u32x4{out[0], out[1], out[2], out[3]}, W + t);
+    W[t] = u32x4{out[0], out[1], out[2], out[3]};
 }
 
 // Blocks of 256 threads for n units as a 2-D grid whose x extent stays at
