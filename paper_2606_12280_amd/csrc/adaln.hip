@@ -155,7 +155,7 @@ __global__ __launch_bounds__(WPB * 64) void adaln_quant_rows_kernel(
         const __amdgpu_buffer_rsrc_t ro =
             make_rsrc(out + (in ? r : 0) * K, in ? static_cast<uint32_t>(K) : 0u);
 #pragma unroll
-        for (int c = 0; c < CH; ++c) store_codes(ro, out_off[c], lo[c], hi[c]);
+        for (int c = 0; c < CH; ++c) store_codes<false>(ro, out_off[c], lo[c], hi[c]);
     };
 
     uint4 x[CH];

@@ -15,8 +15,12 @@
 //   scale, then 8 codes per chunk as one 8-byte store.
 // The smoothed value float(x) * mul is recomputed for the coding pass rather
 // than held, which halves the registers a row needs; it is the same binary32
-// product both times. X is read exactly once and the codes written once,
-// both with nontemporal hints (streamed through the caches, not kept).
+// product both times. X is read exactly once, with nontemporal hints (streamed
+// through the caches, not kept), and the codes written once, a layer's weights
+// with that hint too (see store_codes). On the weight side the first group also
+// writes the reciprocals of the smoothing factors it holds (as a launch of
+// their own 2.2 us and a gap; 16384 x 4096 weights, smoothing factors and codes:
+// 60.3 -> 58.6 us).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -65,7 +69,7 @@ __device__ __forceinline__ float absmax8(const uint4 &x, const float4 &ma, const
 // g + 2 groups, ... With PF the next row is loaded while the current one is
 // reduced and coded. Without (the K = 65536 group has no register room for
 // a second row) a group takes one row and the grid covers the rows.
-template <int G, int CH, int WPB, bool PF>
+template <int G, int CH, int WPB, bool PF, bool WEIGHTS>
 __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
     const uint16_t *__restrict__ src, const float *__restrict__ mul, int64_t R,
     int64_t K, int rows_per_group, int8_t *__restrict__ out, float *__restrict__ scale,
@@ -93,7 +97,7 @@ __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
         ma[c] = live ? m4[2 * col(c)] : make_float4(0.f, 0.f, 0.f, 0.f);
         mb[c] = live ? m4[2 * col(c) + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    if (inv != nullptr && group == 0) {
+    if (WEIGHTS && group == 0) {
         // inv need only be 4-byte aligned
         struct __attribute__((packed, aligned(4))) Eight {
             float v[8];
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
         const __amdgpu_buffer_rsrc_t ro =
             rows::make_rsrc(out + (in ? r : 0) * K, in ? static_cast<uint32_t>(K) : 0u);
 #pragma unroll
-        for (int c = 0; c < CH; ++c) rows::store_codes(ro, col(c) * 8u, lo[c], hi[c]);
+        for (int c = 0; c < CH; ++c) rows::store_codes<WEIGHTS>(ro, col(c) * 8u, lo[c], hi[c]);
     };
 
     uint4 x[CH];
@@ -201,7 +205,7 @@ __global__ __launch_bounds__(WPB * 64) void smooth_quant_rows_kernel(
 
 // One round of groups: as many as the GPU holds at once (fewer for short
 // inputs), each walking an equal share of the rows.
-template <int G, int CH, int WPB, bool PF>
+template <int G, int CH, int WPB, bool PF, bool WEIGHTS>
 hipError_t launch_rows(const uint16_t *src, const float *mul, int64_t R, int64_t K,
                        int8_t *out, float *scale, float *inv, hipStream_t stream) {
     constexpr int SLOTS = WPB / G;
@@ -210,7 +214,7 @@ hipError_t launch_rows(const uint16_t *src, const float *mul, int64_t R, int64_t
     const int64_t rpg =
         PF ? rows::rows_per_group(
                  R, rows::resident_groups(
-                        reinterpret_cast<const void *>(&smooth_quant_rows_kernel<G, CH, WPB, PF>),
+                        reinterpret_cast<const void *>(&smooth_quant_rows_kernel<G, CH, WPB, PF, WEIGHTS>),
                         WPB * 64, SLOTS, resident))
            : 1;
     if (rpg > INT32_MAX) return hipErrorInvalidValue;
@@ -220,7 +224,7 @@ hipError_t launch_rows(const uint16_t *src, const float *mul, int64_t R, int64_t
     // group gets there: R = 2^22 rows with K > 32768, 512 GB of bf16, more
     // than the GPU holds.
     if (blocks * WPB * 64 >= (INT64_C(1) << 32)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((smooth_quant_rows_kernel<G, CH, WPB, PF>),
+    hipLaunchKernelGGL((smooth_quant_rows_kernel<G, CH, WPB, PF, WEIGHTS>),
                        dim3(static_cast<unsigned>(blocks)), dim3(WPB * 64), 0, stream, src, mul,
                        R, K, static_cast<int>(rpg), out, scale, inv);
     return hipGetLastError();
@@ -316,6 +320,22 @@ __global__ void lambda_kernel(const float *__restrict__ s, float *__restrict__ l
     lam[k] = out;
 }
 
+// WEIGHTS: a layer's weights (inv written, codes streamed) or activations.
+template <bool WEIGHTS>
+hipError_t launch_rows_k(const uint16_t *src, const float *mul, int64_t R, int64_t K, int8_t *out,
+                         float *scale, float *inv, hipStream_t stream) {
+    const auto go = [&](auto launcher) { return launcher(src, mul, R, K, out, scale, inv, stream); };
+    // A group covers 512 * G * CH columns; take the smallest that holds K.
+    if (K <= 512) return go(launch_rows<1, 1, 4, true, WEIGHTS>);
+    if (K <= 1024) return go(launch_rows<2, 1, 4, true, WEIGHTS>);
+    if (K <= 2048) return go(launch_rows<4, 1, 4, true, WEIGHTS>);
+    if (K <= 4096) return go(launch_rows<4, 2, 4, true, WEIGHTS>);
+    if (K <= 8192) return go(launch_rows<8, 2, 8, true, WEIGHTS>);
+    if (K <= 16384) return go(launch_rows<8, 4, 8, true, WEIGHTS>);
+    if (K <= 32768) return go(launch_rows<8, 8, 8, true, WEIGHTS>);
+    return go(launch_rows<16, 8, 16, false, WEIGHTS>);  // K <= 65536
+}
+
 unsigned blocks_for(int64_t n, int threads) {
     return static_cast<unsigned>((n + threads - 1) / threads);
 }
@@ -325,15 +345,8 @@ unsigned blocks_for(int64_t n, int threads) {
 hipError_t launch_smooth_quant_rows(const uint16_t *src, const float *mul, int64_t R,
                                     int64_t K, int8_t *out, float *scale, float *inv,
                                     hipStream_t stream) {
-    // A group covers 512 * G * CH columns; take the smallest that holds K.
-    if (K <= 512) return launch_rows<1, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 1024) return launch_rows<2, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 2048) return launch_rows<4, 1, 4, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 4096) return launch_rows<4, 2, 4, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 8192) return launch_rows<8, 2, 8, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 16384) return launch_rows<8, 4, 8, true>(src, mul, R, K, out, scale, inv, stream);
-    if (K <= 32768) return launch_rows<8, 8, 8, true>(src, mul, R, K, out, scale, inv, stream);
-    return launch_rows<16, 8, 16, false>(src, mul, R, K, out, scale, inv, stream);  // K <= 65536
+    return inv != nullptr ? launch_rows_k<true>(src, mul, R, K, out, scale, inv, stream)
+                          : launch_rows_k<false>(src, mul, R, K, out, scale, inv, stream);
 }
 
 hipError_t launch_zero_f32(float *dst, int64_t K, hipStream_t stream) {
